@@ -5,104 +5,27 @@
 // does not write the steps down.  The model here is the standard OOPS EM with
 // a uniform start prior and a fixed background (see projmotif.h).
 //
-// Vector path: one workgroup (4 waves) per model.  The packed instance is
+// Vector path (protein here; DNA in em_dna.hip): one workgroup (4 waves) per model.  The packed instance is
 // staged in LDS; each wave owns whole sequences, so the per-sequence
 // log-sum-exp is a wavefront reduction; the E-step reads the log-odds table
 // from LDS; M-step counts go to per-wave LDS accumulators.
-#include <math.h>
-
-#include "pm_common.h"
+#include "em_vec.h"
 
 namespace pm {
 
-struct EmArgs {
-    pm_inst one;                // the instance, when inst is NULL
-    const pm_inst *inst;        // batch: instance table, or NULL
-    const int32_t *item_inst;   // batch: instance of every trial item
-    const pm_bucket *buckets;   // batch: the models' buckets (their items)
-    const double *theta0;
-    const double *bg;
-    const int64_t *n_dev;
-    double *theta_out;
-    double *J;
-    double *llr;
-    int32_t *sites;
-    int64_t B;
-    int l, iters;
-    int site_stride;  // sites row length (t, or the largest t of a batch)
-    double beta;
-    int model;        // PM_OOPS, PM_ZOOPS or PM_TCM
-    double mix0;      // ZOOPS gamma or TCM lambda of theta0
-    double *mix_out;  // [B] mixing parameter of the final E-step, or NULL
-    int seq_cap;      // LDS words reserved for the packed input (0: read from global)
-    int off_cap;      // LDS offsets reserved (0: read from global)
-};
-
-constexpr int kEmThreads = 256;
-constexpr int kEmWaves = kEmThreads / 64;
-
 template <typename T>
-__device__ __forceinline__ T ninf();
-template <>
-__device__ __forceinline__ float ninf<float>() { return -INFINITY; }
-template <>
-__device__ __forceinline__ double ninf<double>() { return -INFINITY; }
-
-__device__ __forceinline__ float ex(float v) { return expf(v); }
-__device__ __forceinline__ double ex(double v) { return exp(v); }
-__device__ __forceinline__ float lg1p(float v) { return log1pf(v); }
-__device__ __forceinline__ double lg1p(double v) { return log1p(v); }
-
-// ln(e^u + e^v), e^{-inf} = 0
-template <typename T>
-__device__ __forceinline__ T log_add(T u, T v)
-{
-    if (u == ninf<T>()) return v;
-    if (v == ninf<T>()) return u;
-    const T d = u - v;
-    return (d > 0 ? u : v) + lg1p(ex(d > 0 ? -d : d));
-}
-
-template <typename V>
-__device__ __forceinline__ V block_sum(V v, V *red)
-{
-    v = wave_sum(v);
-    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    V r = red[0];
-#pragma unroll
-    for (int w = 1; w < kEmWaves; ++w) r += red[w];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ int64_t wave_min_i64(int64_t v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        int64_t u = __shfl_xor(v, o);
-        v = u < v ? u : v;
-    }
-    return v;
-}
-
-template <typename T, int A>
 __device__ __forceinline__ T score_at(const uint32_t *W, int64_t P, const T *Wt, int l)
 {
     T s = 0;
-    if (A == 4) {
-        uint32_t hi, lo;
-        dna_window(W, P, hi, lo);
-        for (int p = 0; p < l; ++p) s += Wt[dna_at(hi, lo, p) * l + p];
-    } else {
-        for (int p = 0; p < l; ++p) s += Wt[prot_sym(W, P + p) * l + p];
-    }
+    for (int p = 0; p < l; ++p) s += Wt[prot_sym(W, P + p) * l + p];
     return s;
 }
 
-template <typename T, int A>
+// Protein models.
+template <typename T>
 __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
 {
+    constexpr int A = 20;
     const int64_t b = blockIdx.x;
     int64_t nvalid = a.n_dev ? *a.n_dev : a.B;
     if (nvalid > a.B) nvalid = a.B;
@@ -122,7 +45,7 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
     const int tid = threadIdx.x, wv = tid >> 6, lane = lane_id();
     const int l = a.l, t = I.t, AL = A * l;
     const double beta = a.beta;
-    const int seq_words = a.seq_cap ? (int)(A == 4 ? (I.n_total + 15) / 16 + 4 : (I.n_total + 5) / 6 + 4) : 0;
+    const int seq_words = a.seq_cap ? (int)((I.n_total + 5) / 6 + 4) : 0;
 
     for (int i = tid; i < AL; i += kEmThreads) th[i] = a.theta0[b * AL + i];
     for (int i = tid; i < seq_words; i += kEmThreads) seq[i] = I.packed[i];
@@ -160,7 +83,7 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
                 int64_t ba = 0;
                 T *ac = acc[wv];
                 for (int64_t x = lane; x < L; x += 64) {
-                    const T s = score_at<T, A>(W, s0 + x, Wt, l);
+                    const T s = score_at<T>(W, s0 + x, Wt, l);
                     const T v = lm + s;
                     const T li = log_add(ln0, v);
                     lsum += (double)li;
@@ -173,13 +96,7 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
                     }
                     const T z = v == ninf<T>() ? (T)0 : ex(v - li);
                     const int64_t P = s0 + x;
-                    if (A == 4) {
-                        uint32_t hi, lo;
-                        dna_window(W, P, hi, lo);
-                        for (int p = 0; p < l; ++p) atomicAdd(&ac[dna_at(hi, lo, p) * l + p], z);
-                    } else {
-                        for (int p = 0; p < l; ++p) atomicAdd(&ac[prot_sym(W, P + p) * l + p], z);
-                    }
+                    for (int p = 0; p < l; ++p) atomicAdd(&ac[prot_sym(W, P + p) * l + p], z);
                 }
                 llr_w += wave_sum(lsum);
                 if (last && a.sites) {
@@ -197,7 +114,7 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
             double sm = 0;
             int64_t ba = 0;
             for (int64_t x = lane; x < L; x += 64) {
-                const T s = score_at<T, A>(W, s0 + x, Wt, l);
+                const T s = score_at<T>(W, s0 + x, Wt, l);
                 const bool up = s > mx;
                 const T e = ex(up ? mx - s : s - mx);
                 sm = up ? sm * (double)e + 1.0 : (s > ninf<T>() ? sm + (double)e : sm);
@@ -236,16 +153,10 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
                 T *ac = acc[wv];
                 const T zo = (T)zoff;
                 for (int64_t x = lane; x < L; x += 64) {
-                    const T s = score_at<T, A>(W, s0 + x, Wt, l);
+                    const T s = score_at<T>(W, s0 + x, Wt, l);
                     const T z = ex(s + zo);
                     const int64_t P = s0 + x;
-                    if (A == 4) {
-                        uint32_t hi, lo;
-                        dna_window(W, P, hi, lo);
-                        for (int p = 0; p < l; ++p) atomicAdd(&ac[dna_at(hi, lo, p) * l + p], z);
-                    } else {
-                        for (int p = 0; p < l; ++p) atomicAdd(&ac[prot_sym(W, P + p) * l + p], z);
-                    }
+                    for (int p = 0; p < l; ++p) atomicAdd(&ac[prot_sym(W, P + p) * l + p], z);
                 }
             }
         }
@@ -287,10 +198,10 @@ __global__ void __launch_bounds__(kEmThreads) k_em_vec(const EmArgs a)
     if (tid == 0 && a.mix_out) a.mix_out[b] = mix;
 }
 
-template <typename T, int A>
+template <typename T>
 static int launch_em(const EmArgs &a, size_t lds, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_em_vec<T, A>), dim3((unsigned)a.B), dim3(kEmThreads), lds, st, a);
+    hipLaunchKernelGGL(k_em_vec<T>, dim3((unsigned)a.B), dim3(kEmThreads), lds, st, a);
     PM_LAUNCHED();
     return PM_OK;
 }
@@ -413,9 +324,8 @@ static int vec_launch(EmArgs &a, int A, int32_t precision, int64_t nw_max, int t
     a.seq_cap = nw_max * 4 <= 48 * 1024 ? (int)nw_max : 0;
     a.off_cap = (t_max + 1) * 8 <= 8 * 1024 ? t_max + 1 : 0;
     const size_t lds = ((a.seq_cap + 1) & ~1) * 4 + (size_t)a.off_cap * 8;
-    if (A == 4)
-        return precision == PM_FP64 ? launch_em<double, 4>(a, lds, st) : launch_em<float, 4>(a, lds, st);
-    return precision == PM_FP64 ? launch_em<double, 20>(a, lds, st) : launch_em<float, 20>(a, lds, st);
+    if (A == 4) return launch_em_dna(a, precision == PM_FP64, lds, st);
+    return precision == PM_FP64 ? launch_em<double>(a, lds, st) : launch_em<float>(a, lds, st);
 }
 
 extern "C" size_t pm_em_workspace(const pm_seqs *S, int32_t l, int32_t precision)

@@ -1,0 +1,85 @@
+// Shared pieces of the vector EM kernels of libprojmotif (gfx950): the launch
+// arguments and the helpers of a workgroup of four waves that takes one model.
+#pragma once
+
+#include <math.h>
+
+#include "pm_common.h"
+
+namespace pm {
+
+struct EmArgs {
+    pm_inst one;                // the instance, when inst is NULL
+    const pm_inst *inst;        // batch: instance table, or NULL
+    const int32_t *item_inst;   // batch: instance of every trial item
+    const pm_bucket *buckets;   // batch: the models' buckets (their items)
+    const double *theta0;
+    const double *bg;
+    const int64_t *n_dev;
+    double *theta_out;
+    double *J;
+    double *llr;
+    int32_t *sites;
+    int64_t B;
+    int l, iters;
+    int site_stride;  // sites row length (t, or the largest t of a batch)
+    double beta;
+    int model;        // PM_OOPS, PM_ZOOPS or PM_TCM
+    double mix0;      // ZOOPS gamma or TCM lambda of theta0
+    double *mix_out;  // [B] mixing parameter of the final E-step, or NULL
+    int seq_cap;      // LDS words reserved for the packed input (0: read from global)
+    int off_cap;      // LDS offsets reserved (0: read from global)
+};
+
+constexpr int kEmThreads = 256;
+constexpr int kEmWaves = kEmThreads / 64;
+
+template <typename T>
+__device__ __forceinline__ T ninf();
+template <>
+__device__ __forceinline__ float ninf<float>() { return -INFINITY; }
+template <>
+__device__ __forceinline__ double ninf<double>() { return -INFINITY; }
+
+__device__ __forceinline__ float ex(float v) { return expf(v); }
+__device__ __forceinline__ double ex(double v) { return exp(v); }
+__device__ __forceinline__ float lg1p(float v) { return log1pf(v); }
+__device__ __forceinline__ double lg1p(double v) { return log1p(v); }
+
+// ln(e^u + e^v), e^{-inf} = 0
+template <typename T>
+__device__ __forceinline__ T log_add(T u, T v)
+{
+    if (u == ninf<T>()) return v;
+    if (v == ninf<T>()) return u;
+    const T d = u - v;
+    return (d > 0 ? u : v) + lg1p(ex(d > 0 ? -d : d));
+}
+
+template <typename V>
+__device__ __forceinline__ V block_sum(V v, V *red)
+{
+    v = wave_sum(v);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    V r = red[0];
+#pragma unroll
+    for (int w = 1; w < kEmWaves; ++w) r += red[w];
+    __syncthreads();
+    return r;
+}
+
+__device__ __forceinline__ int64_t wave_min_i64(int64_t v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        int64_t u = __shfl_xor(v, o);
+        v = u < v ? u : v;
+    }
+    return v;
+}
+
+// the DNA form (em_dna.hip); a.seq_cap and a.off_cap are set, lds their bytes
+int launch_em_dna(const EmArgs &a, bool fp64, size_t lds, hipStream_t st);
+
+}  // namespace pm
