@@ -188,6 +188,31 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
     return v;
 }
 
+// v of the lane that a DPP control names, `none` in lanes that have no such
+// lane or lie in a row the mask leaves out
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or(double v, double none)
+{
+    const uint64_t n = __builtin_bit_cast(uint64_t, none), s = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)n, (int)(uint32_t)s, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(n >> 32), (int)(s >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// inclusive prefix sum of doubles over the 64 lanes, by lane moves in the
+// vector unit (row shifts, then the last lane of each row to the next rows)
+// rather than LDS permutes
+__device__ __forceinline__ double wave_incl_sum(double v)
+{
+    v += dpp_or<0x111, 0xf>(v, 0.0);
+    v += dpp_or<0x112, 0xf>(v, 0.0);
+    v += dpp_or<0x114, 0xf>(v, 0.0);
+    v += dpp_or<0x118, 0xf>(v, 0.0);
+    v += dpp_or<0x142, 0xa>(v, 0.0);
+    v += dpp_or<0x143, 0xc>(v, 0.0);
+    return v;
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
 
