@@ -7,7 +7,9 @@
 // the posteriors are a softmax over windows, so one pass over a sequence is
 // an attention-like sweep with a reference maximum and rescaled accumulators.
 //
-// Arithmetic: v_mfma_f32_16x16x32_f16.  The one-hot side is exact in FP16.
+// Arithmetic: the E-step on v_smfmac_f32_16x16x64_f16 (the one-hot operand as
+// the 2-of-4 sparse one, see Tiles), the M-step on v_mfma_f32_16x16x32_f16.
+// The one-hot side is exact in FP16.
 // The other side is split in two FP16 halves, x = hi + lo with
 // hi = fp16(x) and lo = fp16(x - hi), both multiplied by the same one-hot
 // operand, so every product is exact and the operand carries about 22
@@ -26,10 +28,14 @@
 // Lane layout of one 16x16x32 MFMA (lane L, r = L % 16, g = L / 16):
 //   A operand: row r, the g-th group of 8 contraction indices;
 //   B operand: column r, the same 8 contraction indices;
-//   D:         column r, rows 4g .. 4g+3.
+//   D:         column r, rows 4g .. 4g+3;
+// of one 16x16x64 sparse MFMA:
+//   A operand: row r, of the indices 16g .. 16g+15 two in every four (8 values
+//              and their places, 2 bits each);
+//   B operand: column r, indices 8g .. 8g+7 and 32+8g .. 32+8g+7.
 // E-step: rows = 16 windows, columns = 16 models, contraction = (position,
-// letter) pairs, position-major.  Lane (r, g) of k-block kb carries positions
-// 8kb+2g and 8kb+2g+1.  M-step: rows = 16 (position, letter) pairs, columns =
+// letter) pairs, position-major, 16 positions (a fragment) per instruction.
+// M-step: rows = 16 (position, letter) pairs, columns =
 // models, contraction = 32 windows (two E tiles); lane (r, g) carries windows
 // 4g..4g+3 of the first tile and of the second, exactly the rows its E-step
 // outputs hold, so posteriors feed the M-step without leaving registers.
@@ -37,7 +43,8 @@
 // Softmax reference: scores leave the E-step already shifted by the current
 // reference (the accumulator starts at -reference), and the reference moves
 // only when a score passes it by more than kSlack, so the common path needs
-// neither a cross-lane maximum nor a rescale.  Posteriors enter the M-step as
+// neither a cross-lane maximum nor a rescale.  It starts just under the
+// sequence's largest score of the previous iteration (sweep).  Posteriors enter the M-step as
 // 2^(S - ref + kPOff) <= 2^(kPOff + kSlack) = 2^15, inside the FP16 range.
 // The reference moves by whole numbers, so every rescale (of the count
 // accumulators and of the FP64 sums) is an exact power of two.
@@ -54,6 +61,17 @@
 // packed instance in global memory.  (G, PPB) is the tunable tile
 // shape: em_autotune times the variants on the caller's models and records
 // the fastest per (ceil(l/4), precision) class.
+//
+// What bounds it: vector issue.  An MFMA takes two of the vector unit's issue
+// slots (8 cycles) and overlaps the rest of its 16, so a pair of 16 MFMAs and
+// 44 vector instructions, 8 of them exponentials, takes about 350 cycles of a
+// SIMD; 600 are measured at three waves per SIMD ((18,6), 89 000 models, 10
+// iterations: 10.4 ms).  Measured on that workload: 12.0 ms with the dense
+// E-step, references started from the lowest score and two FP64 logarithms
+// per sequence; 11.8 with the sparse E-step (16 instead of 20 MFMAs a pair),
+// 10.3 in a timing copy whose references never move.  (15,4) batch of 24
+// instances: 18.1 -> 15.4 ms; single FP16, (21,7), 16 384 models, 5 iterations:
+// 6.8 -> 6.3 ms.
 #include <math.h>
 #include <stddef.h>
 #include <stdlib.h>
@@ -63,6 +81,7 @@
 namespace pm {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte table quad
@@ -91,6 +110,9 @@ struct EmMfmaArgs {
     // kernel; tbase: first slot of every instance of a batch (NULL: one instance)
     const uint8_t *tables;
     const int64_t *tbase;
+    // instances of at most mcap sequences keep every sequence's largest score
+    // of the previous iteration in LDS (0: none)
+    int mcap;
 };
 
 // workgroups of a launch that takes mw models per workgroup: whole groups of
@@ -121,6 +143,16 @@ constexpr int kShapeDefault = 14;  // untuned
 constexpr int kMaxMT2 = 6;         // G = 2 for ceil(l/4) <= 6 (registers)
 constexpr float kPOff = 3.0f;
 constexpr float kSlack = 12.0f;
+// A known sequence's reference starts this far below its largest score of the
+// iteration before: room for it to fall by kBelow + kPOff bits (else the
+// iteration is repeated) and to rise by kSlack - kBelow (else the reference
+// moves).  On the (12,4) to (24,7) shapes the largest score of a sequence
+// changes by -8 to +8 bits from theta0 to theta1 (medians near +2, 1% beyond
+// -6 and +5) and by less than 6 bits either way afterwards.
+constexpr float kBelowFirst = 8.0f;  // iteration 1
+constexpr float kBelow = 4.0f;       // later ones
+constexpr float kTopMin = 0.0f;  // smallest largest shifted score of such a sweep: a term of 1, whose
+                                 // FP16 halves still hold 24 bits down to 2^-24
 
 // 32 DNA symbols starting at P (MSB-first) as hi (P..P+15) and lo (P+16..P+31).
 // CLAMP: reads clamped below nw (global memory); otherwise the buffer is padded.
@@ -177,31 +209,55 @@ __device__ __forceinline__ uint32_t pack_hi(float p0, float p1)
     return __builtin_bit_cast(uint32_t, half2v{(_Float16)p0, (_Float16)p1});
 }
 
-// E-step k-blocks (8 positions each) for MT M-tiles (4 positions each)
+// E-step contraction for MT M-tiles (4 MT positions).  A window's one-hot has
+// one 1 in every four columns (a position's letters), which is inside the
+// 2-of-4 pattern of the sparse matrix instruction, so the E-step runs on
+// v_smfmac_f32_16x16x64_f16: 16 positions per instruction where the dense
+// form takes 8, at the same rate.  Of a position's four letters the A operand
+// stores the pair that holds the symbol (letters 0, 1 or 2, 3: the index
+// field) as (1, 0) or (0, 1).  A fragment covers 16 positions, position 4g+i
+// of it in lane group g; a last fragment of at most 8 positions (eight)
+// repeats them in groups 2, 3, so that the split form's hi and lo halves
+// share one instruction.
 template <int MT>
 struct Tiles {
-    static constexpr int LB = (MT + 1) / 2;
+    static constexpr int FULL = MT / 4;                        // fragments of 16 positions
+    static constexpr int REST = 4 * MT % 16;                   // positions of the last one
+    static constexpr bool EIGHT = REST == 4 || REST == 8;      // repeated in groups 2, 3
+    static constexpr int NF = FULL + (REST != 0 ? 1 : 0);      // fragments of a window
     static constexpr int CX = 4 * MT;       // count rows (positions) of a model
     static constexpr int NE = 4 * MT + 12;  // M-step table entries a pair reads
+    static constexpr int NEV = MT <= 4 ? 44 : MT <= 6 ? 52 : 60;  // E-step entries a pair reads
+    // up to 24 positions the index fields have room behind the E-step entries
+    // (dword e: those of entries e and e + 16, the two tiles of a pair);
+    // beyond, an entry keeps the high bytes of its eight halves and its field
+    static constexpr bool BYTES = MT > 6;
+    // matrix instructions per tile: hi and lo of every fragment, one for both
+    // in a repeated one
+    static constexpr int ops(bool split) { return split ? 2 * NF - (EIGHT ? 1 : 0) : NF; }
 };
-
-// Split form with an odd number of 4-position tiles: the last k-block holds
-// at most four real positions, so its hi and lo halves share one MFMA (lane
-// groups 0, 1 carry the hi halves of its positions, groups 2, 3 the lo halves
-// of the same positions) instead of two MFMAs each half zero.
-template <int MT, bool SPLIT>
-constexpr bool kMergeTail = SPLIT && (MT & 1) != 0;
 
 // one-hot tables of one window pair: the symbols at s0 + a0 + e
 template <int MT>
 struct alignas(16) PairTables {
-    uint32_t oh2[64][4];          // letters 0..3 of symbol e, then of symbol e+1
+    uint32_t ev[64][4];           // E-step entries: symbols e .. e+3, then the index fields
     uint4 mt8[Tiles<MT>::NE][4];  // [e][c]: symbols e..e+3 and e+16..e+19 == c
 };
+static_assert(Tiles<4>::NEV * 16 + 28 * 4 <= 1024 && Tiles<6>::NEV * 16 + 36 * 4 <= 1024, "room for the index fields");
 // 16-byte quads of one pair's tables: at most 256, one per thread of a workgroup
 template <int MT>
 constexpr int kTabQuads = (int)(sizeof(PairTables<MT>) / 16);
 static_assert(kTabQuads<8> <= 256, "one quad per thread");
+
+// The index field of four symbols (8 bits, first on top): for each, the
+// first on the lowest nibble, its pair of letters as two 2-bit row numbers.
+__device__ __forceinline__ uint32_t index_field(uint32_t y)
+{
+    uint32_t f = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f |= ((y >> (7 - 2 * i)) & 1u ? 0xEu : 0x4u) << (4 * i);
+    return f;
+}
 
 // lut[y]: four FP16 halves, half q = 1.0 where 2-bit field q of y (from the top)
 // is zero.  With y = (4 symbols) ^ (c * 0x55) that is the one-hot of letter c.
@@ -215,7 +271,8 @@ __device__ __forceinline__ void build_lut(uint2 *lut)
 }
 
 // Workgroup-cooperative build: thread (e = tid / 4, c = tid % 4) writes
-// mt8[e][c] (e < NE) and word c of oh2[e].
+// mt8[e][c] (e < NE) and word c of E-step entry e, or a dword of the index
+// fields behind the entries.
 template <int MT, bool CLAMP>
 __device__ __forceinline__ void build_tables(const uint32_t *W, int64_t nw, int64_t base, const uint2 *lut,
                                              PairTables<MT> &T)
@@ -229,48 +286,97 @@ __device__ __forceinline__ void build_tables(const uint32_t *W, int64_t nw, int6
         const uint2 u0 = lut[(hi >> 24) ^ cc], u1 = lut[(lo >> 24) ^ cc];
         T.mt8[e][c] = make_uint4(u0.x, u0.y, u1.x, u1.y);
     }
-    // word c of oh2[e]: letters 2(c&1), 2(c&1)+1 of symbol e (c < 2) or e+1
-    const uint32_t sym = c < 2 ? hi >> 30 : (hi >> 28) & 3u;
-    T.oh2[e][c] = (sym >> 1) == (c & 1u) ? 0x3C00u << ((sym & 1u) << 4) : 0u;
+    const uint32_t y = hi >> 24;  // symbols e .. e+3
+    if (Tiles<MT>::BYTES) {
+        uint32_t v = 0;
+        if (c < 2) {
+            // halves of symbols 2c, 2c+1: high byte of 1.0 in the half of the letter's parity
+            v = (0x3Cu << (((y >> (6 - 4 * c)) & 1u) * 8)) | (0x3C0000u << (((y >> (4 - 4 * c)) & 1u) * 8));
+        } else if (c == 2) {
+            v = index_field(y);
+        }
+        T.ev[e][c] = v;
+    } else {
+        constexpr int NEV = Tiles<MT>::NEV;
+        if (e < NEV) T.ev[e][c] = 0x3C00u << (((y >> (6 - 2 * c)) & 1u) << 4);
+        // entry e's thread c == 0 also writes dword e of the index fields
+        if (c == 0 && e < 4 * (64 - NEV))
+            (&T.ev[NEV][0])[e] = index_field(y) | (index_field(lo >> 24) << 16);
+    }
 }
 
 struct SeqState {
     float4v neg;  // kPOff - mref in every component: the E-step accumulators' start
     float mref;   // reference (log2 units) of the scores
+    float top;    // largest shifted score so far
     double srun;  // this lane's share of sum 2^(S - mref + kPOff), in FP64
     float bestv;  // final E-step: best score and window of this lane
     int besti;
 };
 
-// One pair of 16-window tiles (windows a0 .. a0+31 of one sequence) for this
-// wave's G groups of 16 models; the groups share the A operands.
 // LDS byte offsets of this lane's fragments within a pair's tables, formed
-// once per kernel: E-step A (positions 2g, 2g+1 of window r), the same for a
-// merged last k-block (positions 2(g & 1), 2(g & 1)+1), M-step A
+// once per sequence: the E-step entry of window r and position 4g, the same
+// for a repeated fragment (position 4 (g & 1)), M-step A
 struct FragOff {
-    uint32_t a, a_merged, m;
+    uint32_t a, a_eight, m;
 };
 
+// the A operand of an E-step fragment: stored values and index field
+struct SparseA {
+    half8 v;
+    int ix;
+};
+
+// the operands of fragment f for the two tiles of a pair
+template <int MT>
+__device__ __forceinline__ void sparse_frag(const char *tb, const FragOff &fo, int f, SparseA (&A)[2])
+{
+    const bool eight = Tiles<MT>::EIGHT && f == Tiles<MT>::FULL;
+    const uint32_t off = (eight ? fo.a_eight : fo.a) + 256u * f;
+    if (Tiles<MT>::BYTES) {
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(tb + off + 256 * t2);
+            // bytes to halves: (0, b0, 0, b1)
+            uint4 w;
+            w.x = __builtin_amdgcn_perm(0u, q.x, 0x010C000Cu);
+            w.y = __builtin_amdgcn_perm(0u, q.x, 0x030C020Cu);
+            w.z = __builtin_amdgcn_perm(0u, q.y, 0x010C000Cu);
+            w.w = __builtin_amdgcn_perm(0u, q.y, 0x030C020Cu);
+            A[t2].v = __builtin_bit_cast(half8, w);
+            A[t2].ix = (int)q.z;
+        }
+    } else {
+        // one dword for both tiles, the second's in the high half
+        const int ix = *reinterpret_cast<const int *>(tb + 16 * Tiles<MT>::NEV + off / 4);
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+            A[t2].v = *reinterpret_cast<const half8 *>(tb + off + 256 * t2);
+            A[t2].ix = ix;
+        }
+    }
+}
+
+template <int MT, int TILE>
+__device__ __forceinline__ float4v smfma(const SparseA &A, half16 W, float4v S)
+{
+    // the field's half of the dword: the second tile's is the high one
+    return __builtin_amdgcn_smfmac_f32_16x16x64_f16(A.v, W, S, A.ix, 0, TILE == 1 && !Tiles<MT>::BYTES ? 1 : 0);
+}
+
+// One pair of 16-window tiles (windows a0 .. a0+31 of one sequence) for this
+// wave's G groups of 16 models; the groups share the A operands.
 template <int MT, bool LAST, bool TAIL, bool SPLIT, int G>
 __device__ __forceinline__ void tile_pair(int a0, int L, const PairTables<MT> &T, const FragOff &fo,
-                                          const half8 (&Whi)[G][Tiles<MT>::LB],
-                                          const half8 (&Wlo)[G][Tiles<MT>::LB], float4v (&O)[G][MT],
+                                          const half16 (&Wb)[G][Tiles<MT>::ops(SPLIT)], float4v (&O)[G][MT],
                                           SeqState (&st)[G])
 {
-    constexpr int LB = Tiles<MT>::LB;
-    constexpr bool MERGE = kMergeTail<MT, SPLIT>;
-    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    constexpr int NF = Tiles<MT>::NF;
+    const int lane = threadIdx.x & 63, g = lane >> 4;
     const char *tb = reinterpret_cast<const char *>(&T);
-    half8 Ae[2][LB];
+    SparseA Ae[NF][2];
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int kb = 0; kb < LB; ++kb) {
-            // entry 16 t2 + 8 kb + (r + 2g) of oh2 (16 B each); a merged last
-            // block's groups 2, 3 repeat the positions of groups 0, 1
-            const uint32_t off = MERGE && kb == LB - 1 ? fo.a_merged : fo.a;
-            Ae[t2][kb] = *reinterpret_cast<const half8 *>(tb + off + (16 * t2 + 8 * kb) * 16);
-        }
+    for (int f = 0; f < NF; ++f) sparse_frag<MT>(tb, fo, f, Ae[f]);
     // E-step, already shifted: S' = S - (mref - kPOff); one chain per tile and group
     float4v S0[G], S1[G];
 #pragma unroll
@@ -279,15 +385,12 @@ __device__ __forceinline__ void tile_pair(int a0, int L, const PairTables<MT> &T
         S1[q] = st[q].neg;
     }
 #pragma unroll
-    for (int kb = 0; kb < LB; ++kb)
+    for (int op = 0; op < Tiles<MT>::ops(SPLIT); ++op)
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            S0[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ae[0][kb], Whi[q][kb], S0[q], 0, 0, 0);
-            S1[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ae[1][kb], Whi[q][kb], S1[q], 0, 0, 0);
-            if (SPLIT && !(MERGE && kb == LB - 1)) {
-                S0[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ae[0][kb], Wlo[q][kb], S0[q], 0, 0, 0);
-                S1[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ae[1][kb], Wlo[q][kb], S1[q], 0, 0, 0);
-            }
+            const int f = SPLIT ? op / 2 : op;
+            S0[q] = smfma<MT, 0>(Ae[f][0], Wb[q][op], S0[q]);
+            S1[q] = smfma<MT, 1>(Ae[f][1], Wb[q][op], S1[q]);
         }
     half8 Am[MT];
     if (!LAST) {
@@ -298,34 +401,33 @@ __device__ __forceinline__ void tile_pair(int a0, int L, const PairTables<MT> &T
     }
 #pragma unroll
     for (int q = 0; q < G; ++q) {
-        float S[8];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            S[j] = S0[q][j];
-            S[4 + j] = S1[q][j];
-        }
         if (TAIL) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (a0 + 16 * (u >> 2) + 4 * g + (u & 3) >= L) S[u] = -INFINITY;
+            for (int u = 0; u < 4; ++u) {
+                if (a0 + 4 * g + u >= L) S0[q][u] = -INFINITY;
+                if (a0 + 16 + 4 * g + u >= L) S1[q][u] = -INFINITY;
+            }
         }
-        // the common path needs only whether a score passed the slack, not the
-        // maximum (which fmaxf would form after quieting each operand)
-        bool big = false;
+        // the largest shifted score of the sequence so far: passes the slack, or
+        // the best start, only when one of these eight does
+        const float top = fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(st[q].top, S0[q][0]), S0[q][1]), S0[q][2]),
+                                S0[q][3]), S1[q][0]), S1[q][1]), S1[q][2]), S1[q][3]);
+        st[q].top = top;
+        // a new best start is rare: the eight scores are looked at one by one
+        // only where their maximum passes the best so far
+        if (LAST && __ballot(top - st[q].neg[0] > st[q].bestv)) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) big |= S[u] > kPOff + kSlack;
-        if (LAST) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (S[u] - st[q].neg[0] > st[q].bestv) {
-                    st[q].bestv = S[u] - st[q].neg[0];
+            for (int u = 0; u < 8; ++u) {
+                const float v = (u < 4 ? S0[q][u & 3] : S1[q][u & 3]) - st[q].neg[0];
+                if (v > st[q].bestv) {
+                    st[q].bestv = v;
                     st[q].besti = a0 + 16 * (u >> 2) + 4 * g + (u & 3);
                 }
+            }
         }
-        if (__builtin_expect(__ballot(big) != 0, 0)) {
+        if (__builtin_expect(__ballot(top > kPOff + kSlack) != 0, 0)) {
             // rare: move the reference up to the model's new maximum
-            float tm = fmaxf(fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])), fmaxf(fmaxf(S[4], S[5]), fmaxf(S[6], S[7])));
-            tm = fmaxf(tm, __shfl_xor(tm, 16));
+            float tm = fmaxf(top, __shfl_xor(top, 16));
             tm = fmaxf(tm, __shfl_xor(tm, 32));
             // a whole number of binades, so that the rescales below are exact
             const float d = tm > kPOff + kSlack ? ceilf(tm - kPOff) : 0.f;
@@ -334,11 +436,18 @@ __device__ __forceinline__ void tile_pair(int a0, int L, const PairTables<MT> &T
             if (!LAST)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) O[q][mt] *= al;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) S[u] -= d;
+            S0[q] -= d;
+            S1[q] -= d;
+            st[q].top -= d;
             st[q].mref += d;
             const float n = kPOff - st[q].mref;  // exactly what the scores are shifted by
             st[q].neg = float4v{n, n, n, n};
+        }
+        float S[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            S[j] = S0[q][j];
+            S[4 + j] = S1[q][j];
         }
         float P[8];
 #pragma unroll
@@ -375,25 +484,33 @@ __device__ __forceinline__ void tile_pair(int a0, int L, const PairTables<MT> &T
 // window a0 of sequence i (kSrcPre): loaded into registers one step ahead of
 // their use, written to LDS at the step that uses them.
 template <int MT, int PPB>
-__device__ __forceinline__ void fetch_tables(const EmMfmaArgs &a, int64_t slot0, int L, int a0, u32x4 (&pf)[PPB])
+__device__ __forceinline__ void fetch_tables(const EmMfmaArgs &a, int slot0, int L, int a0, u32x4 (&pf)[PPB])
 {
     // every load is unconditional and in bounds (a pair past the sequence's
     // end re-reads the step's first pair, threads past the quads re-read the
     // last one), which keeps pf in registers; only the LDS writes are guarded
     constexpr int NQ = kTabQuads<MT>;
     const int q = (int)threadIdx.x < NQ ? (int)threadIdx.x : NQ - 1;
-    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.tables) + (slot0 + a0 / 32) * NQ + q;
+    // slot0 and L are scalars: one scalar base, one lane offset for all loads
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.tables) + ((int64_t)slot0 + a0 / 32) * NQ;
 #pragma unroll
-    for (int u = 0; u < PPB; ++u) pf[u] = src[(a0 + 32 * u < L ? u : 0) * NQ];
+    for (int u = 0; u < PPB; ++u) pf[u] = (src + (a0 + 32 * u < L ? u : 0) * NQ)[(uint32_t)q];
 }
 
 // windows and first table slot of sequence i of the instance whose first slot
-// is tb (kSrcPre)
-__device__ __forceinline__ void seq_slots(const EmMfmaArgs &a, int64_t tb, int i, int &L, int64_t &slot0)
+// is tb (kSrcPre), as scalars (a launch has fewer than 2^31 slots)
+__device__ __forceinline__ void seq_slots(const EmMfmaArgs &a, int64_t tb, int i, int &L, int &slot0)
 {
-    L = (int)(a.offsets[i + 1] - a.offsets[i]) - a.l + 1;
-    slot0 = tb + seq_slot0(a.offsets, i, a.l);
+    L = __builtin_amdgcn_readfirstlane((int)(a.offsets[i + 1] - a.offsets[i])) - a.l + 1;
+    slot0 = __builtin_amdgcn_readfirstlane((int)(tb + seq_slot0(a.offsets, i, a.l)));
 }
+
+// A model's log-likelihood over the sequences so far: sum of log2 references
+// and exponents, and the product of the mantissas of its sums (its logarithm
+// is taken once per iteration).
+struct LogSum {
+    double e, m;
+};
 
 // One sequence: every window pair (tables built by the whole workgroup, or
 // copied from the precomputed ones), then the per-sequence log-sum-exp and
@@ -401,37 +518,47 @@ __device__ __forceinline__ void seq_slots(const EmMfmaArgs &a, int64_t tb, int i
 // the count accumulators of group q.  kSrcPre: pf holds this thread's quads of
 // the sequence's first step on entry and of the step after the sequence (the
 // next sequence's first, or sequence 0's for the next iteration) on return.
+//
+// mprev: this lane's slots (one per group) of the sequence's largest score in
+// the previous iteration (NULL: not kept).  The reference starts `below` under
+// it (known[q]), so that it seldom moves: a move costs a wave about a window
+// pair's time, and when all models start from their lowest score some model of
+// the 16 moves in most pairs of a sequence's first third.  A model whose
+// scores all stay under kTopMin of such a start would lose bits of its
+// posteriors: low[q] is set, and the caller repeats the iteration with that
+// model's references from its lowest score (again: the others start as they
+// did before, from the slot's high byte).
 template <int MT, int SRC, bool LAST, bool SPLIT, int PPB, int G>
 __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, const uint2 *lut, int i, int64_t bw,
                                       int64_t nvalid, PairTables<MT> *tabs, int &parity, int64_t tb,
                                       u32x4 (&pf)[PPB], float (*acc)[16][Tiles<MT>::CX][4],
-                                      const half8 (&Whi)[G][Tiles<MT>::LB], const half8 (&Wlo)[G][Tiles<MT>::LB],
-                                      const float (&mlow)[G], double (&llr)[G])
+                                      const half16 (&Wb)[G][Tiles<MT>::ops(SPLIT)], const float (&mlow)[G],
+                                      int16_t *mprev, const bool (&known)[G], float below, bool again, bool (&low)[G],
+                                      LogSum (&llr)[G])
 {
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int64_t s0 = a.offsets[i];
     const int L = (int)(a.offsets[i + 1] - s0) - a.l + 1;
     static_assert(offsetof(PairTables<MT>, mt8) == 1024, "M-step fragments follow the 1 KB of E-step ones");
-    const FragOff fo{(uint32_t)(r + 2 * g) * 16u, (uint32_t)(r + 2 * (g & 1)) * 16u,
+    const FragOff fo{(uint32_t)(r + 4 * g) * 16u, (uint32_t)(r + 4 * (g & 1)) * 16u,
                      1024u + (uint32_t)((4 * g + (r >> 2)) * 4 + (r & 3)) * 16u};
-    // kSrcPre: this sequence's first slot and the next sequence's size and
-    // first slot, formed once here rather than at every step
-    int64_t sl = 0, sln = 0;
-    int Ln = 0;
+    // kSrcPre: this sequence's and the next one's size and first slot, formed
+    // once here rather than at every step
+    int sl = 0, sln = 0, Ls = 0, Ln = 0;
     if constexpr (SRC == kSrcPre) {
-        int Li;
-        seq_slots(a, tb, i, Li, sl);
+        seq_slots(a, tb, i, Ls, sl);
         seq_slots(a, tb, i + 1 < a.t ? i + 1 : 0, Ln, sln);
     }
     float4v O[G][MT];
     SeqState st[G];
+    int prev[G];  // largest score of the previous iteration
 #pragma unroll
     for (int q = 0; q < G; ++q) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) O[q][mt] = float4v{0.f, 0.f, 0.f, 0.f};
-        // the reference starts at the lowest score the model can give
-        const float n0 = kPOff - mlow[q];
-        st[q] = SeqState{float4v{n0, n0, n0, n0}, mlow[q], 0.0, -INFINITY, 0};
+        prev[q] = mprev ? (again ? mprev[16 * q] >> 8 : (int)(int8_t)mprev[16 * q]) : 0;
+        const float m0 = known[q] ? (float)prev[q] - below : mlow[q], n0 = kPOff - m0;
+        st[q] = SeqState{float4v{n0, n0, n0, n0}, m0, -INFINITY, 0.0, -INFINITY, 0};
     }
     for (int a0 = 0; a0 < L; a0 += 32 * PPB) {
         PairTables<MT> *T = tabs + PPB * parity;
@@ -444,35 +571,48 @@ __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, co
         } else {
 #pragma unroll
             for (int u = 0; u < PPB; ++u)
-                if (a0 + 32 * u < L) build_tables<MT, SRC == kSrcGlobal>(W, a.nwords, s0 + a0 + 32 * u, lut, T[u]);
+                if (a0 + 32 * u < L)
+                    build_tables<MT, SRC == kSrcGlobal>(W, a.nwords, s0 + a0 + 32 * u, lut, T[u]);
         }
         __syncthreads();
         if constexpr (SRC == kSrcPre) {
             // the next step's quads (this sequence's, or the next sequence's
             // first) load while this step computes
             const int na = a0 + 32 * PPB;
-            if (na < L) fetch_tables<MT, PPB>(a, sl, L, na, pf);
+            if (na < Ls) fetch_tables<MT, PPB>(a, sl, Ls, na, pf);
             else fetch_tables<MT, PPB>(a, sln, Ln, 0, pf);
         }
 #pragma unroll
         for (int u = 0; u < PPB; ++u) {
             const int b0 = a0 + 32 * u;
-            if (b0 + 32 <= L) tile_pair<MT, LAST, false, SPLIT, G>(b0, L, T[u], fo, Whi, Wlo, O, st);
-            else if (b0 < L) tile_pair<MT, LAST, true, SPLIT, G>(b0, L, T[u], fo, Whi, Wlo, O, st);
+            if (b0 + 32 <= L) tile_pair<MT, LAST, false, SPLIT, G>(b0, L, T[u], fo, Wb, O, st);
+            else if (b0 < L) tile_pair<MT, LAST, true, SPLIT, G>(b0, L, T[u], fo, Wb, O, st);
         }
     }
 #pragma unroll
     for (int q = 0; q < G; ++q) {
+        // the sequence's largest score, to the next whole number, for the next
+        // iteration (every lane of the model holds the same)
+        if (mprev) {
+            float tp = st[q].top;
+            tp = fmaxf(tp, __shfl_xor(tp, 16));
+            tp = fmaxf(tp, __shfl_xor(tp, 32));
+            low[q] |= known[q] && !(tp >= kTopMin);
+            const float m = fminf(fmaxf(ceilf(st[q].mref + tp - kPOff), -128.f), 127.f);
+            mprev[16 * q] = (int16_t)(((int)m & 0xff) | (prev[q] << 8));
+        }
         // the model's sum over the sequence's windows: the four lane groups'
         // FP64 partials combined in FP64
         double sr = st[q].srun;
         sr += __shfl_xor(sr, 16);
         sr += __shfl_xor(sr, 32);
-        const double ln2 = 0.6931471805599453;
-        const double lse = ((double)st[q].mref - (double)kPOff) * ln2 + log(sr);
-        llr[q] += lse - log((double)L);
+        const double m = __builtin_amdgcn_frexp_mant(sr) * llr[q].m;
+        llr[q].e += (double)st[q].mref + (double)(__builtin_amdgcn_frexp_exp(sr) + __builtin_amdgcn_frexp_exp(m));
+        llr[q].m = __builtin_amdgcn_frexp_mant(m);
         if (!LAST) {
-            const float inv = (float)(1.0 / sr);
+            double x = __builtin_amdgcn_rcp(sr);
+            x = fma(fma(-sr, x, 1.0), x, x);
+            const float inv = (float)x;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 float4v *dst = reinterpret_cast<float4v *>(&acc[q][r][4 * mt + g][0]);
@@ -504,6 +644,13 @@ constexpr int em_static_lds()
 {
     return 2 * PPB * (int)sizeof(PairTables<MT>) + 256 * (int)sizeof(uint2) + kWaves * G * 16 * Tiles<MT>::CX * 16;
 }
+// LDS of one sequence's largest scores: a whole number per model
+template <int G>
+constexpr int kPrevBytes = kWaves * G * 16 * 2;
+// Instances of up to this many sequences keep them: up to ceil(l/4) = 5 the
+// workgroups of a CU leave as much LDS in every tile shape, and a limit of
+// its own per shape would make results depend on the shape.
+constexpr int kPrevT = 60;
 template <int MT, int PPB, int G>
 constexpr int em_waves_per_simd()
 {
@@ -514,11 +661,12 @@ constexpr int em_waves_per_simd()
 template <int MT, int SRC, bool SPLIT, int PPB, int G>
 __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())) k_em_mfma(const EmMfmaArgs a0)
 {
-    constexpr int LB = Tiles<MT>::LB, CX = Tiles<MT>::CX, MW = 16 * kWaves * G;
+    constexpr int NF = Tiles<MT>::NF, CX = Tiles<MT>::CX, MW = 16 * kWaves * G;
     __shared__ __align__(16) PairTables<MT> tabs[2 * PPB];
-    __shared__ __align__(16) uint2 lut[256];
+    __shared__ __align__(16) uint2 lut[SRC == kSrcGlobal ? 256 : 1];
     __shared__ __align__(16) float accs[kWaves][G][16][CX][4];
     __shared__ float lbg2[4];  // log2 bg[c], formed once for every iteration's log-odds
+    extern __shared__ __align__(16) int16_t prevs[];  // [mcap][models of the workgroup]
 
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     EmMfmaArgs a = a0;
@@ -553,8 +701,7 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
     const uint2 *lutp = nullptr;
     u32x4 pf[PPB];
     if constexpr (SRC == kSrcPre) {
-        int L0;
-        int64_t sl0;
+        int L0, sl0;
         seq_slots(a, tb, 0, L0, sl0);
         fetch_tables<MT, PPB>(a, sl0, L0, 0, pf);  // the first step of the first sweep
     } else {
@@ -570,17 +717,23 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
     const int l = a.l, t = a.t, AL = 4 * l;
     const double beta = a.beta;
     int parity = 0;
+    int16_t *mprev = t <= a.mcap ? prevs + 16 * G * wv + r : nullptr;
+    // sum of ln L_i over the sequences
+    double lnL = 0;
+    for (int i = lane; i < t; i += 64) lnL += log((double)((int)(a.offsets[i + 1] - a.offsets[i]) - l + 1));
+    lnL = wave_sum(lnL);
 
-    half8 Whi[G][LB], Wlo[G][LB];
+    half16 Wb[G][Tiles<MT>::ops(SPLIT)];
     for (int it = 0; it <= a.iters; ++it) {
         const bool last = it == a.iters;
         const double *src = it == 0 ? a.theta0 : a.theta_out;
         // ---- log-odds (log2 units) of the lane's E-step B operands: model r of
-        // group q, positions 8kb+2g and 8kb+2g+1, letters 0..3, split in two
-        // FP16 halves (a merged last block: hi halves in groups 0, 1, lo halves
-        // of the same positions in groups 2, 3); the lane's hi entries cover
-        // every position once across the four lane groups, so the prior and the
-        // lowest score are lane sums over them
+        // group q, of every fragment positions 2g, 2g+1 (entries 0..7: letters 0..3
+        // of both) and 8+2g, 8+2g+1 (entries 8..15), split in two FP16 halves, one
+        // operand each; a repeated fragment has positions 2g, 2g+1 only, hi in
+        // entries 0..7 and lo in 8..15 of one operand.  Every position is held once
+        // across the four lane groups, so the prior and the lowest score are lane
+        // sums over them
         double prior[G];
         float mlow[G];
         // the lane's position base goes through an empty asm statement so that
@@ -595,33 +748,43 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
             double pr = 0;
             float wmin = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < LB; ++kb) {
-                const bool lo_half = kMergeTail<MT, SPLIT> && kb == LB - 1 && g2 >= 4;
-                half8 hi, lo;
+            for (int f = 0; f < NF; ++f) {
+                const bool eight = Tiles<MT>::EIGHT && f == Tiles<MT>::FULL;
+                half16 hi = {}, lo = {};
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int p = 8 * kb + (lo_half ? g2 - 4 : g2) + h;
+                for (int h = 0; h < (eight ? 2 : 4); ++h) {
+                    const int p = 16 * f + 8 * (h >> 1) + g2 + (h & 1);
                     float mn = 0.f;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         float w = 0.f;
                         if (p < l && vb) {
                             const double th = src[b * AL + c * l + p];
-                            if (it == 0 && !lo_half) a.theta_out[b * AL + c * l + p] = th;
+                            if (it == 0) a.theta_out[b * AL + c * l + p] = th;
                             // log2 theta by the hardware FP32 logarithm (about 2^-23
                             // relative, within what the split FP16 halves carry)
                             const float l2 = __builtin_amdgcn_logf((float)th);
                             w = l2 - lbg2[c];
-                            if (!lo_half) pr += a.bg[c] * (double)l2;  // log2 units
+                            pr += a.bg[c] * (double)l2;  // log2 units
                         }
                         mn = c == 0 ? w : fminf(mn, w);
-                        hi[4 * h + c] = (_Float16)w;
-                        lo[4 * h + c] = (_Float16)(w - (float)hi[4 * h + c]);
+                        const _Float16 wh = (_Float16)w;
+                        hi[4 * h + c] = wh;
+                        lo[4 * h + c] = (_Float16)(w - (float)wh);
                     }
-                    if (!lo_half) wmin += mn;
+                    wmin += mn;
                 }
-                Whi[q][kb] = lo_half ? lo : hi;
-                Wlo[q][kb] = lo;
+                if (eight) {
+                    if (SPLIT)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) hi[8 + j] = lo[j];
+                    Wb[q][SPLIT ? 2 * f : f] = hi;
+                } else if (SPLIT) {
+                    Wb[q][2 * f] = hi;
+                    Wb[q][SPLIT ? 2 * f + 1 : f] = lo;
+                } else {
+                    Wb[q][f] = hi;
+                }
             }
             pr += __shfl_xor(pr, 16);
             pr += __shfl_xor(pr, 32);
@@ -631,25 +794,45 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
             // lowest possible score, a little below to absorb rounding
             mlow[q] = wmin - 1.0f;
         }
-        // ---- clear the count accumulators (own entries)
+        LogSum ls[G];
+        bool known[G];
+        const float below = it == 1 ? kBelowFirst : kBelow;
 #pragma unroll
-        for (int q = 0; q < G; ++q)
+        for (int q = 0; q < G; ++q) known[q] = mprev && it > 0;
+        for (bool again = false;; again = true) {
+            // ---- clear the count accumulators (own entries)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                *reinterpret_cast<float4v *>(&acc[q][r][4 * mt + g][0]) = float4v{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();  // tables free
-
+            for (int q = 0; q < G; ++q) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *reinterpret_cast<float4v *>(&acc[q][r][4 * mt + g][0]) = float4v{0.f, 0.f, 0.f, 0.f};
+                ls[q] = LogSum{0.0, 1.0};
+            }
+            __syncthreads();  // tables free
+            bool low[G] = {};
+            for (int i = 0; i < t; ++i) {
+                int16_t *mp = mprev ? mprev + (int64_t)i * MW : nullptr;
+                if (last)
+                    sweep<MT, SRC, true, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Wb, mlow,
+                                                        mp, known, below, again, low, ls);
+                else
+                    sweep<MT, SRC, false, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Wb,
+                                                         mlow, mp, known, below, again, low, ls);
+            }
+            // repeated at most once: the low models then start from their lowest score
+            if (!mprev || it == 0 || again) break;
+            bool any = false;
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                any |= low[q];
+                known[q] = !low[q];
+            }
+            if (!__syncthreads_or(any)) break;
+        }
         double llr[G];
 #pragma unroll
-        for (int q = 0; q < G; ++q) llr[q] = 0;
-        for (int i = 0; i < t; ++i) {
-            if (last)
-                sweep<MT, SRC, true, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Whi, Wlo,
-                                                    mlow, llr);
-            else
-                sweep<MT, SRC, false, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Whi, Wlo,
-                                                     mlow, llr);
-        }
+        for (int q = 0; q < G; ++q)
+            llr[q] = (ls[q].e - (double)t * (double)kPOff) * 0.6931471805599453 + log(ls[q].m) - lnL;
         // ---- objective of theta^it, then the M-step (own entries)
 #pragma unroll
         for (int q = 0; q < G; ++q) {
@@ -785,12 +968,15 @@ template <int MT, bool SPLIT, int PPB, int G>
 static int launch_em_mfma(const EmMfmaArgs &a, hipStream_t st)
 {
     const int64_t groups = em_groups(a, 16 * kWaves * G);
+    EmMfmaArgs b = a;
+    b.mcap = a.site_stride < kPrevT ? a.site_stride : kPrevT;  // site_stride: the most sequences of an instance
+    const size_t lds = (size_t)b.mcap * kPrevBytes<G>;
     if (a.tables)
-        hipLaunchKernelGGL((k_em_mfma<MT, kSrcPre, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), 0, st,
-                           a);
+        hipLaunchKernelGGL((k_em_mfma<MT, kSrcPre, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), lds, st,
+                           b);
     else
-        hipLaunchKernelGGL((k_em_mfma<MT, kSrcGlobal, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), 0,
-                           st, a);
+        hipLaunchKernelGGL((k_em_mfma<MT, kSrcGlobal, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), lds,
+                           st, b);
     PM_LAUNCHED();
     return PM_OK;
 }
