@@ -71,7 +71,7 @@
 // per sequence; 11.8 with the sparse E-step (16 instead of 20 MFMAs a pair),
 // 10.3 in a timing copy whose references never move.  (15,4) batch of 24
 // instances: 18.1 -> 15.4 ms; single FP16, (21,7), 16 384 models, 5 iterations:
-// 6.8 -> 6.3 ms.
+// 6.8 -> 6.3 ms, 3.8 ms in three parts.
 #include <math.h>
 #include <stddef.h>
 #include <stdlib.h>
@@ -136,7 +136,14 @@ __host__ __device__ inline PlanView plan_view(const int64_t *plan, int P)
     return PlanView{plan, plan + P + 1, plan + 2 * P + 1, plan + 3 * P + 1};
 }
 
-constexpr int kWaves = 4;  // waves (groups of 16 models) per workgroup
+constexpr int kWaves = 4;  // waves (groups of 16 models) per part of a workgroup
+// A workgroup has up to three parts of kWaves waves, each taking all the
+// models but only every parts-th sequence, with its own tables and counts; the
+// parts' counts and log-likelihoods are added at the end of an iteration.  A
+// launch takes several parts (of one group of models per wave) where its
+// models alone would leave SIMDs idle: see em_parts.
+constexpr int kPartThreads = 64 * kWaves;
+__device__ __forceinline__ int part_thread() { return (int)(threadIdx.x % kPartThreads); }
 // tile shape 10 G + PPB: G groups of 16 models per wave, PPB window pairs
 // built per workgroup barrier
 constexpr int kShapeDefault = 14;  // untuned
@@ -263,7 +270,7 @@ __device__ __forceinline__ uint32_t index_field(uint32_t y)
 // is zero.  With y = (4 symbols) ^ (c * 0x55) that is the one-hot of letter c.
 __device__ __forceinline__ void build_lut(uint2 *lut)
 {
-    const uint32_t y = threadIdx.x;  // the workgroup has 256 threads
+    const uint32_t y = part_thread();  // the parts of a workgroup write the same
     uint32_t h[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) h[q] = ((y >> (6 - 2 * q)) & 3u) ? 0u : 0x3C00u;
@@ -277,7 +284,7 @@ template <int MT, bool CLAMP>
 __device__ __forceinline__ void build_tables(const uint32_t *W, int64_t nw, int64_t base, const uint2 *lut,
                                              PairTables<MT> &T)
 {
-    const int tid = threadIdx.x, e = tid >> 2;
+    const int tid = part_thread(), e = tid >> 2;
     const uint32_t c = tid & 3u;
     uint32_t hi, lo;
     dna32<CLAMP>(W, base + e, nw, hi, lo);
@@ -490,7 +497,7 @@ __device__ __forceinline__ void fetch_tables(const EmMfmaArgs &a, int slot0, int
     // end re-reads the step's first pair, threads past the quads re-read the
     // last one), which keeps pf in registers; only the LDS writes are guarded
     constexpr int NQ = kTabQuads<MT>;
-    const int q = (int)threadIdx.x < NQ ? (int)threadIdx.x : NQ - 1;
+    const int q = part_thread() < NQ ? part_thread() : NQ - 1;
     // slot0 and L are scalars: one scalar base, one lane offset for all loads
     const u32x4 *src = reinterpret_cast<const u32x4 *>(a.tables) + ((int64_t)slot0 + a0 / 32) * NQ;
 #pragma unroll
@@ -516,8 +523,8 @@ struct LogSum {
 // copied from the precomputed ones), then the per-sequence log-sum-exp and
 // counts, or, in the final E-step, the best start of every model.  acc[q]:
 // the count accumulators of group q.  kSrcPre: pf holds this thread's quads of
-// the sequence's first step on entry and of the step after the sequence (the
-// next sequence's first, or sequence 0's for the next iteration) on return.
+// the sequence's first step on entry and the first step of sequence `next` (the
+// part's next one, or its first for the next iteration) on return.
 //
 // mprev: this lane's slots (one per group) of the sequence's largest score in
 // the previous iteration (NULL: not kept).  The reference starts `below` under
@@ -531,7 +538,7 @@ struct LogSum {
 template <int MT, int SRC, bool LAST, bool SPLIT, int PPB, int G>
 __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, const uint2 *lut, int i, int64_t bw,
                                       int64_t nvalid, PairTables<MT> *tabs, int &parity, int64_t tb,
-                                      u32x4 (&pf)[PPB], float (*acc)[16][Tiles<MT>::CX][4],
+                                      u32x4 (&pf)[PPB], int next, float (*acc)[16][Tiles<MT>::CX][4],
                                       const half16 (&Wb)[G][Tiles<MT>::ops(SPLIT)], const float (&mlow)[G],
                                       int16_t *mprev, const bool (&known)[G], float below, bool again, bool (&low)[G],
                                       LogSum (&llr)[G])
@@ -547,7 +554,7 @@ __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, co
     int sl = 0, sln = 0, Ls = 0, Ln = 0;
     if constexpr (SRC == kSrcPre) {
         seq_slots(a, tb, i, Ls, sl);
-        seq_slots(a, tb, i + 1 < a.t ? i + 1 : 0, Ln, sln);
+        seq_slots(a, tb, next, Ln, sln);
     }
     float4v O[G][MT];
     SeqState st[G];
@@ -566,8 +573,8 @@ __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, co
         if constexpr (SRC == kSrcPre) {
 #pragma unroll
             for (int u = 0; u < PPB; ++u)
-                if (a0 + 32 * u < L && threadIdx.x < kTabQuads<MT>)
-                    reinterpret_cast<u32x4 *>(&T[u])[threadIdx.x] = pf[u];
+                if (a0 + 32 * u < L && part_thread() < kTabQuads<MT>)
+                    reinterpret_cast<u32x4 *>(&T[u])[part_thread()] = pf[u];
         } else {
 #pragma unroll
             for (int u = 0; u < PPB; ++u)
@@ -640,9 +647,14 @@ __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, co
 // the registers of ceil(l/4) <= 5 allow it and three workgroups' LDS (with 6 KB
 // of headroom each) fit the 160 KB of a CU, else two
 template <int MT, int PPB, int G>
+constexpr int em_part_lds()
+{
+    return 2 * PPB * (int)sizeof(PairTables<MT>) + kWaves * G * 16 * Tiles<MT>::CX * 16;
+}
+template <int MT, int PPB, int G>
 constexpr int em_static_lds()
 {
-    return 2 * PPB * (int)sizeof(PairTables<MT>) + 256 * (int)sizeof(uint2) + kWaves * G * 16 * Tiles<MT>::CX * 16;
+    return em_part_lds<MT, PPB, G>() + 256 * (int)sizeof(uint2);
 }
 // LDS of one sequence's largest scores: a whole number per model
 template <int G>
@@ -656,19 +668,34 @@ constexpr int em_waves_per_simd()
 {
     return MT <= 5 && 3 * (em_static_lds<MT, PPB, G>() + 6 * 1024) <= 160 * 1024 ? 3 : 2;
 }
+// parts of a workgroup at most: a wave per SIMD each, as many as the registers
+// of ceil(l/4) allow
+constexpr int em_max_parts(int mt, bool split) { return mt <= 5 || (mt == 6 && !split) ? 3 : 2; }
+constexpr int kPartsPPB = 4;  // window pairs per barrier of a workgroup of several parts
 
-// G groups of 16 models per wave, kWaves waves per workgroup
-template <int MT, int SRC, bool SPLIT, int PPB, int G>
-__global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())) k_em_mfma(const EmMfmaArgs a0)
+// G groups of 16 models per wave, kWaves waves per part; PARTS: several parts
+template <int MT, int SRC, bool SPLIT, int PPB, int G, bool PARTS>
+__global__ void __launch_bounds__((PARTS ? kPartThreads * em_max_parts(MT, SPLIT) : kPartThreads),
+                                  (PARTS ? em_max_parts(MT, SPLIT) : em_waves_per_simd<MT, PPB, G>()))
+k_em_mfma(const EmMfmaArgs a0)
 {
     constexpr int NF = Tiles<MT>::NF, CX = Tiles<MT>::CX, MW = 16 * kWaves * G;
-    __shared__ __align__(16) PairTables<MT> tabs[2 * PPB];
+    typedef float Acc[kWaves][G][16][CX][4];
     __shared__ __align__(16) uint2 lut[SRC == kSrcGlobal ? 256 : 1];
-    __shared__ __align__(16) float accs[kWaves][G][16][CX][4];
     __shared__ float lbg2[4];  // log2 bg[c], formed once for every iteration's log-odds
-    extern __shared__ __align__(16) int16_t prevs[];  // [mcap][models of the workgroup]
+    // per part: tables [2 PPB] and counts; then [mcap][models of the workgroup]
+    extern __shared__ __align__(16) uint8_t dynlds[];
+    constexpr int kPart = em_part_lds<MT, PPB, G>();
+    const int parts = PARTS ? (int)(blockDim.x / kPartThreads) : 1;
+    const int part = PARTS ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kPartThreads)) : 0;
+    PairTables<MT> *tabs = reinterpret_cast<PairTables<MT> *>(dynlds + part * kPart);
+    auto acc_of = [&](int q) -> Acc & {
+        return *reinterpret_cast<Acc *>(dynlds + q * kPart + 2 * PPB * (int)sizeof(PairTables<MT>));
+    };
+    Acc &accs = acc_of(part);
+    int16_t *prevs = reinterpret_cast<int16_t *>(dynlds + parts * kPart);
 
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int wv = part_thread() >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     EmMfmaArgs a = a0;
     int64_t b0, nvalid, tb = 0;
     if (a0.inst) {
@@ -702,7 +729,7 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
     u32x4 pf[PPB];
     if constexpr (SRC == kSrcPre) {
         int L0, sl0;
-        seq_slots(a, tb, 0, L0, sl0);
+        seq_slots(a, tb, part < a.t ? part : 0, L0, sl0);
         fetch_tables<MT, PPB>(a, sl0, L0, 0, pf);  // the first step of the first sweep
     } else {
         build_lut(lut);
@@ -722,6 +749,21 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
     double lnL = 0;
     for (int i = lane; i < t; i += 64) lnL += log((double)((int)(a.offsets[i + 1] - a.offsets[i]) - l + 1));
     lnL = wave_sum(lnL);
+    // a step has one barrier: a part with fewer steps than another waits at the
+    // barriers of those it does not have
+    int idle = 0;
+    if (parts > 1) {
+        int mine = 0, most = 0;
+        for (int q = 0; q < parts; ++q) {
+            int n = 0;
+            for (int i = q + parts * lane; i < t; i += 64 * parts)
+                n += ((int)(a.offsets[i + 1] - a.offsets[i]) - l + 32 * PPB) / (32 * PPB);
+            n = wave_sum(n);
+            most = n > most ? n : most;
+            mine = q == part ? n : mine;
+        }
+        idle = __builtin_amdgcn_readfirstlane(most - mine);
+    }
 
     half16 Wb[G][Tiles<MT>::ops(SPLIT)];
     for (int it = 0; it <= a.iters; ++it) {
@@ -810,15 +852,17 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
             }
             __syncthreads();  // tables free
             bool low[G] = {};
-            for (int i = 0; i < t; ++i) {
+            for (int i = part; i < t; i += parts) {
                 int16_t *mp = mprev ? mprev + (int64_t)i * MW : nullptr;
+                const int next = i + parts < t ? i + parts : part;
                 if (last)
-                    sweep<MT, SRC, true, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Wb, mlow,
-                                                        mp, known, below, again, low, ls);
+                    sweep<MT, SRC, true, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, next, acc, Wb,
+                                                        mlow, mp, known, below, again, low, ls);
                 else
-                    sweep<MT, SRC, false, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, acc, Wb,
+                    sweep<MT, SRC, false, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, next, acc, Wb,
                                                          mlow, mp, known, below, again, low, ls);
             }
+            for (int k = 0; k < idle; ++k) __syncthreads();
             // repeated at most once: the low models then start from their lowest score
             if (!mprev || it == 0 || again) break;
             bool any = false;
@@ -829,25 +873,43 @@ __global__ void __launch_bounds__(64 * kWaves, (em_waves_per_simd<MT, PPB, G>())
             }
             if (!__syncthreads_or(any)) break;
         }
+        // the parts' log-likelihoods, added in order (through the tables' LDS,
+        // which nobody reads any more after the barrier)
+        if (parts > 1) {
+            LogSum *comb = reinterpret_cast<LogSum *>(dynlds);  // [part][models of the workgroup]
+            __syncthreads();
+            if (g == 0) comb[part * MW + 16 * wv + r] = ls[0];
+            __syncthreads();
+            ls[0] = LogSum{0.0, 1.0};
+            for (int q = 0; q < parts; ++q) {
+                const LogSum o = comb[q * MW + 16 * wv + r];
+                const double m = o.m * ls[0].m;
+                ls[0].e += o.e + (double)__builtin_amdgcn_frexp_exp(m);
+                ls[0].m = __builtin_amdgcn_frexp_mant(m);
+            }
+        }
         double llr[G];
 #pragma unroll
         for (int q = 0; q < G; ++q)
             llr[q] = (ls[q].e - (double)t * (double)kPOff) * 0.6931471805599453 + log(ls[q].m) - lnL;
-        // ---- objective of theta^it, then the M-step (own entries)
+        // ---- objective of theta^it, then the M-step (own entries; the parts share
+        // the positions)
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const int64_t b = bw + 16 * q + r;
             const bool vb = b < nvalid;
-            if (g == 0 && vb) {
+            if (g == 0 && vb && part == 0) {
                 a.J[b * (a.iters + 1) + it] = llr[q] + beta * prior[q];
                 if (a.llr) a.llr[b * (a.iters + 1) + it] = llr[q];
             }
             if (!last && vb) {
                 #pragma unroll 1
-                for (int mt = 0; mt < MT; ++mt) {
+                for (int mt = part; mt < MT; mt += parts) {
                     const int p = 4 * mt + g;
                     if (p < l) {
-                        const float4v cn = *reinterpret_cast<const float4v *>(&acc[q][r][p][0]);
+                        float4v cn = *reinterpret_cast<const float4v *>(&acc_of(0)[wv][q][r][p][0]);
+                        for (int k = 1; k < parts; ++k)
+                            cn += *reinterpret_cast<const float4v *>(&acc_of(k)[wv][q][r][p][0]);
                         // every column's counts sum to t: normalising by the column's
                         // own total is the same update and stays on the simplex
                         const double tot = (double)cn[0] + (double)cn[1] + (double)cn[2] + (double)cn[3] + beta;
@@ -964,19 +1026,35 @@ static int prepare_tables(EmMfmaArgs &a, const pm_seqs *S, int l, void *ws, size
     return PM_OK;
 }
 
-template <int MT, bool SPLIT, int PPB, int G>
+constexpr int kCUs = 256;
+
+// Parts of a launch's workgroups: as many as leave every CU's wave slots
+// filled, by the workgroups of 64 models alone (in every tile shape, so that
+// results do not depend on the shape).  16 384 models of the (21,7) workload
+// in single FP16, one workgroup per CU: 6.3 ms in one part, 4.3 in two, 3.8 in
+// three.
+static int em_parts(const EmMfmaArgs &a)
+{
+    const int most = em_max_parts((a.l + 3) / 4, a.split != 0);
+    const int64_t groups = em_groups(a, 16 * kWaves);
+    int64_t n = (int64_t)most * kCUs / (groups > 0 ? groups : 1);
+    if (n > a.site_stride) n = a.site_stride;
+    return n < 1 ? 1 : n > most ? most : (int)n;
+}
+
+template <int MT, bool SPLIT, int PPB, int G, bool PARTS = false>
 static int launch_em_mfma(const EmMfmaArgs &a, hipStream_t st)
 {
     const int64_t groups = em_groups(a, 16 * kWaves * G);
     EmMfmaArgs b = a;
     b.mcap = a.site_stride < kPrevT ? a.site_stride : kPrevT;  // site_stride: the most sequences of an instance
-    const size_t lds = (size_t)b.mcap * kPrevBytes<G>;
-    if (a.tables)
-        hipLaunchKernelGGL((k_em_mfma<MT, kSrcPre, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), lds, st,
-                           b);
-    else
-        hipLaunchKernelGGL((k_em_mfma<MT, kSrcGlobal, SPLIT, PPB, G>), dim3((unsigned)groups), dim3(64 * kWaves), lds,
-                           st, b);
+    const int parts = PARTS ? em_parts(a) : 1;
+    const size_t lds = (size_t)parts * em_part_lds<MT, PPB, G>() + (size_t)b.mcap * kPrevBytes<G>;
+    const dim3 grid((unsigned)groups), block(kPartThreads * parts);
+    auto kernel = a.tables ? k_em_mfma<MT, kSrcPre, SPLIT, PPB, G, PARTS> : k_em_mfma<MT, kSrcGlobal, SPLIT, PPB, G, PARTS>;
+    if (lds > 64 * 1024)
+        (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, b);
     PM_LAUNCHED();
     return PM_OK;
 }
@@ -996,18 +1074,18 @@ static int tuned_shape(int l, bool split)
     return v ? v : kShapeDefault;
 }
 
-template <bool SPLIT, int PPB, int G>
+template <bool SPLIT, int PPB, int G, bool PARTS = false>
 static int dispatch_mt(const EmMfmaArgs &a, hipStream_t st)
 {
     switch ((a.l + 3) / 4) {
-    case 1: return launch_em_mfma<1, SPLIT, PPB, G>(a, st);
-    case 2: return launch_em_mfma<2, SPLIT, PPB, G>(a, st);
-    case 3: return launch_em_mfma<3, SPLIT, PPB, G>(a, st);
-    case 4: return launch_em_mfma<4, SPLIT, PPB, G>(a, st);
-    case 5: return launch_em_mfma<5, SPLIT, PPB, G>(a, st);
-    case 6: return launch_em_mfma<6, SPLIT, PPB, G>(a, st);
-    case 7: if (G == 1) return launch_em_mfma<7, SPLIT, PPB, 1>(a, st); break;
-    default: if (G == 1) return launch_em_mfma<8, SPLIT, PPB, 1>(a, st); break;
+    case 1: return launch_em_mfma<1, SPLIT, PPB, G, PARTS>(a, st);
+    case 2: return launch_em_mfma<2, SPLIT, PPB, G, PARTS>(a, st);
+    case 3: return launch_em_mfma<3, SPLIT, PPB, G, PARTS>(a, st);
+    case 4: return launch_em_mfma<4, SPLIT, PPB, G, PARTS>(a, st);
+    case 5: return launch_em_mfma<5, SPLIT, PPB, G, PARTS>(a, st);
+    case 6: return launch_em_mfma<6, SPLIT, PPB, G, PARTS>(a, st);
+    case 7: if (G == 1) return launch_em_mfma<7, SPLIT, PPB, 1, PARTS>(a, st); break;
+    default: if (G == 1) return launch_em_mfma<8, SPLIT, PPB, 1, PARTS>(a, st); break;
     }
     return fail(PM_EINVAL, "tile shape with %d model groups per wave needs l <= %d", G, 4 * kMaxMT2);
 }
@@ -1015,6 +1093,7 @@ static int dispatch_mt(const EmMfmaArgs &a, hipStream_t st)
 template <bool SPLIT>
 static int dispatch_shape(const EmMfmaArgs &a, hipStream_t st, int shape)
 {
+    if (em_parts(a) > 1) return dispatch_mt<SPLIT, kPartsPPB, 1, true>(a, st);
     switch (shape) {
     case 11: return dispatch_mt<SPLIT, 1, 1>(a, st);
     case 12: return dispatch_mt<SPLIT, 2, 1>(a, st);
@@ -1025,11 +1104,21 @@ static int dispatch_shape(const EmMfmaArgs &a, hipStream_t st, int shape)
     }
 }
 
-// shape 0: the one recorded for this length class and precision
-static int dispatch_em_mfma(const EmMfmaArgs &a, hipStream_t st, int shape = 0)
+// the tile shape a launch runs in (0: the one recorded for the length class and
+// precision)
+static int launch_shape(const EmMfmaArgs &a, int shape)
 {
     if (!shape) shape = tuned_shape(a.l, a.split != 0);
     if (!shape_ok(shape, a.l)) shape = 10 + shape % 10;
+    // two groups of models per wave halve the workgroups; where there are too
+    // few already, and the workgroups come in parts, one group per wave
+    return em_parts(a) > 1 ? 10 + kPartsPPB : shape;
+}
+
+// shape 0: the one recorded for this length class and precision
+static int dispatch_em_mfma(const EmMfmaArgs &a, hipStream_t st, int shape = 0)
+{
+    shape = launch_shape(a, shape);
     return a.split ? dispatch_shape<true>(a, st, shape) : dispatch_shape<false>(a, st, shape);
 }
 
@@ -1144,20 +1233,6 @@ int em_refine_mfma_batch(const pm_batch *Bt, int64_t nw_max, int t_max, const pm
     int64_t *plan = reinterpret_cast<int64_t *>(w);
     int64_t *tbase = reinterpret_cast<int64_t *>(w + plan_bytes(Bt->P));
     uint8_t *tables = w + plan_bytes(Bt->P) + tbase_bytes(Bt->P);
-    int shape = tuned_shape(Bt->l, split);
-    if (!shape_ok(shape, Bt->l)) shape = 10 + shape % 10;
-    hipLaunchKernelGGL(k_em_plan, dim3(1), dim3(1024), 0, st, Bt->inst, Bt->P, buckets, n_dev, B,
-                       16 * kWaves * (shape / 10), plan, tbase);
-    PM_LAUNCHED();
-    EmTabArgs tt{};
-    tt.inst = Bt->inst;
-    tt.tbase = tbase;
-    tt.P = Bt->P;
-    tt.l = Bt->l;
-    tt.nslots = batch_slots(Bt);
-    tt.tables = tables;
-    const int rc = launch_em_tables(tt, st);
-    if (rc != PM_OK) return rc;
     EmMfmaArgs a{};
     a.split = split;
     a.inst = Bt->inst;
@@ -1177,6 +1252,19 @@ int em_refine_mfma_batch(const pm_batch *Bt, int64_t nw_max, int t_max, const pm
     a.l = Bt->l;
     a.iters = iters;
     a.beta = beta;
+    const int shape = launch_shape(a, 0);
+    hipLaunchKernelGGL(k_em_plan, dim3(1), dim3(1024), 0, st, Bt->inst, Bt->P, buckets, n_dev, B,
+                       16 * kWaves * (shape / 10), plan, tbase);
+    PM_LAUNCHED();
+    EmTabArgs tt{};
+    tt.inst = Bt->inst;
+    tt.tbase = tbase;
+    tt.P = Bt->P;
+    tt.l = Bt->l;
+    tt.nslots = batch_slots(Bt);
+    tt.tables = tables;
+    const int rc = launch_em_tables(tt, st);
+    if (rc != PM_OK) return rc;
     (void)nw_max;
     // every instance wastes at most one partly filled group
     return dispatch_em_mfma(a, st, shape);

@@ -1,8 +1,9 @@
 """The matrix-core EM where its posteriors' references have edges: models whose
 largest scores fall by far more than the margin from one iteration to the next
 (the iteration is repeated from the lowest scores) beside ones whose scores
-rise, more sequences than the kernel keeps maxima of, and every ceil(l/4) class
-of the sparse E-step's operands.  Split FP16 against the FP64 oracle, with the
+rise, more sequences than the kernel keeps maxima of, every ceil(l/4) class of
+the sparse E-step's operands, and lists of few and of many models (workgroups
+of several parts and of one).  Split FP16 against the FP64 oracle, with the
 form's tolerances (1e-5 of the largest |J|, 2e-5 on theta); the single-FP16
 form's first objective within t * l * 2^-11 * max |log2-odds|."""
 import numpy as np
@@ -33,10 +34,10 @@ def _theta0(rng, seqs, l, B):
     return th
 
 
-@pytest.mark.parametrize("t", [9, 60, 61])
+@pytest.mark.parametrize("t,room", [(9, 70), (60, 70), (61, 70), (1, 70), (2, 70), (9, 60000)])
 @pytest.mark.parametrize("l", [3, 7, 11, 14, 18, 22, 26, 30])
-def test_references_and_sparse_operands(l, t):
-    print("[case] em reference", l, t, flush=True)
+def test_references_and_sparse_operands(l, t, room):
+    print("[case] em reference", l, t, room, flush=True)
     rng = np.random.default_rng([l, t])
     seqs = random_sequences(rng, t, [l + int(n) for n in rng.integers(0, 150, size=t)], "dna")
     B, iters, beta = 70, 4, 1.0
@@ -44,12 +45,17 @@ def test_references_and_sparse_operands(l, t):
     r_th, r_J, r_LL, _ = oracle.em(oracle.Seqs(4, seqs), l, th0, bg, iters, beta)
     S = pm.Seqs(4, seqs)
     d = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    n_dev = torch.tensor([B], device="cuda")
+    in0 = torch.zeros((room, 4, l), dtype=torch.float64, device="cuda")
+    in0[:B] = d(th0)
     for prec in (pm.PM_F16X2, pm.PM_F16):
-        th = torch.zeros((B, 4, l), dtype=torch.float64, device="cuda")
-        J = torch.zeros((B, iters + 1), dtype=torch.float64, device="cuda")
+        th = torch.zeros((room, 4, l), dtype=torch.float64, device="cuda")
+        J = torch.zeros((room, iters + 1), dtype=torch.float64, device="cuda")
         LL = torch.zeros_like(J)
-        pm.em_refine(S, l, d(th0), d(bg), B, None, iters, beta, prec, th, J, LL)
+        pm.em_refine(S, l, in0, d(bg), room, n_dev, iters, beta, prec, th, J, LL)
         torch.cuda.synchronize()
+        assert not th[B:].any() and not J[B:].any()
+        th, J, LL = th[:B], J[:B], LL[:B]
         if prec == pm.PM_F16X2:
             scale = np.abs(r_J).max()
             np.testing.assert_allclose(J.cpu().numpy(), r_J, rtol=1e-5, atol=1e-5 * scale)
