@@ -17,11 +17,17 @@
 // Nothing but the bucket records and members reaches HBM; like the fused
 // count-table path, one pass counts (per-slice totals, scanned on the device)
 // and a second identical pass writes.
+#include <algorithm>
+
 #include "hash_dev.h"
 
 namespace pm {
 
 constexpr int kSortCap = 8192;     // (key, window) pairs sorted at once
+constexpr int kFiltCap = 4096;     // the same behind the filter
+constexpr int kFiltLog = 18;       // log2 bits of the filter's first bitmap (it lies in the buffer)
+static_assert(kFiltCap * 64 == 1 << kFiltLog, "the bitmap lies in the sort buffer");
+constexpr int kFiltWindows = 24;   // filtered windows per thread whose keys stay in registers
 constexpr int kCoarseBins = 4096;  // key ranges of the coarse histogram
 constexpr int kCtlWords = 64;      // block-scan partials and round state
 constexpr int kSortWaves = kHashThreads / kWave;
@@ -29,6 +35,8 @@ constexpr int kSortWaves = kHashThreads / kWave;
 struct HsortArgs {
     HashArgs h;
     uint32_t s;
+    int cap;                        // pairs of the sort buffer
+    int filt;                       // log2 bits of the filter's first bitmap (in the sort buffer), 0: no filter
     uint64_t slice_width;           // keys per slice (the last one may be shorter)
     int64_t *tot_b, *tot_m;         // [items * nslices]
     const int64_t *base_b, *base_m; // [items * nslices] (EMIT)
@@ -66,6 +74,10 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint3
     __syncthreads();
 }
 
+// the filter's second bitmap: 2^kFiltFold bits of the first share one of it
+constexpr int kFiltFold = 2;
+__host__ __device__ constexpr int filt_words2(int log2_bits) { return 1 << (log2_bits - kFiltFold - 5); }
+
 // smallest shift whose 2^sh-wide bins cover `range` keys in kCoarseBins bins
 __device__ __forceinline__ int coarse_shift(uint64_t range)
 {
@@ -84,6 +96,7 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
     const int tid = threadIdx.x;
     const int64_t e = (int64_t)blockIdx.x;  // (item, slice) entry
 
+    if (EMIT && g.tot_b[e] == 0) return;  // counted: nothing to write
     const uint32_t mask = a.masks[j];
     if (!mask_ok(a, mask)) {
         if (tid == 0) {
@@ -92,10 +105,12 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
         }
         return;
     }
-    uint64_t *buf = reinterpret_cast<uint64_t *>(smem);  // [kSortCap]
-    uint32_t *hist = smem + 2 * kSortCap;                 // [kCoarseBins]
+    const uint32_t cap = (uint32_t)g.cap;
+    uint64_t *buf = reinterpret_cast<uint64_t *>(smem);  // [cap]
+    uint32_t *hist = smem + 2 * cap;                      // [kCoarseBins]
     uint32_t *ctl = hist + kCoarseBins;                   // [kCtlWords]
-    uint32_t *seq = ctl + kCtlWords;
+    uint32_t *twice = ctl + kCtlWords;                    // filter's second bitmap
+    uint32_t *seq = twice + (g.filt ? filt_words2(g.filt) : 0);
     int32_t *wst = reinterpret_cast<int32_t *>(seq + a.seq_cap);
     const Staged st = stage_input<A>(a, j, seq, wst);
     int pos[K];
@@ -110,7 +125,79 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
     int sh = sh0;
     __syncthreads();
 
+    // A bucket's key occurs at least twice where s >= 2: a bitmap of hashed keys
+    // whose bit is found set marks the key's bit in a second one, and only
+    // windows with that bit are looked at further (keys met once pass by
+    // coincidence, in about one window of ten).  Commonly they all fit the sort
+    // buffer, and the slice is done after one look at its windows and one at
+    // the keys kept from it.
+    auto hashed = [&](uint64_t key) { return ((uint32_t)key * 0x9E3779B1u) >> (32 - g.filt); };
+    auto marked = [&](uint64_t key) {
+        if (!g.filt) return true;
+        const uint32_t h = hashed(key) >> kFiltFold;
+        return ((twice[h >> 5] >> (h & 31u)) & 1u) != 0;
+    };
+    bool whole = false;  // the slice's pairs are in buf
+    uint32_t n_whole = 0;
+    if (g.filt) {
+        uint32_t *once = smem;  // the sort buffer's words
+        for (int b = tid; b < (1 << g.filt) / 32; b += kHashThreads) once[b] = 0;
+        for (int b = tid; b < filt_words2(g.filt); b += kHashThreads) twice[b] = 0;
+        if (tid == 0) ctl[2 * kSortWaves + 2] = 0;
+        __syncthreads();
+        const bool all_keys = s_lo == 0 && s_hi >= (uint64_t)a.nb;
+        auto mark = [&](uint64_t key) {
+            if (!all_keys && (key < s_lo || key >= s_hi)) return;
+            const uint32_t h = hashed(key);
+            if ((atomicOr(once + (h >> 5), 1u << (h & 31u)) >> (h & 31u)) & 1u)
+                atomicOr(twice + (h >> (kFiltFold + 5)), 1u << ((h >> kFiltFold) & 31u));
+        };
+        auto gather = [&](uint64_t key, int64_t w, bool in) {
+            const bool hit = in && (all_keys || (key >= s_lo && key < s_hi)) && marked(key);
+            const uint64_t m = __ballot(hit);
+            if (!m) return;
+            const int first = __ffsll((unsigned long long)m) - 1;
+            uint32_t slot = 0;
+            if (lane_id() == first) slot = atomicAdd(ctl + 2 * kSortWaves + 2, (uint32_t)__popcll(m));
+            slot = (uint32_t)__builtin_amdgcn_readlane((int)slot, first) +
+                   (uint32_t)__popcll(m & ((1ull << lane_id()) - 1));
+            if (hit && slot < cap) buf[slot] = (key << 32) | (uint64_t)w;
+        };
+        uint32_t held[kFiltWindows];
+        int i = 0;
+#pragma unroll
+        for (int q = 0; q < kFiltWindows; ++q) {
+            const int64_t w = (int64_t)q * kHashThreads + tid;
+            held[q] = 0;
+            if (w < x) {
+                held[q] = (uint32_t)window_key<A, K>(a, st, pos, w, i);
+                mark(held[q]);
+            }
+        }
+        const int i_held = i;
+        for (int64_t w = (int64_t)kFiltWindows * kHashThreads + tid; w < x; w += kHashThreads)
+            mark(window_key<A, K>(a, st, pos, w, i));
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kFiltWindows; ++q) {
+            const int64_t w = (int64_t)q * kHashThreads + tid;
+            gather(held[q], w, w < x);
+        }
+        i = i_held;
+        for (int64_t w0 = (int64_t)kFiltWindows * kHashThreads; w0 < x; w0 += kHashThreads) {
+            const int64_t w = w0 + tid;
+            gather(w < x ? window_key<A, K>(a, st, pos, w, i) : 0u, w, w < x);
+        }
+        __syncthreads();
+        n_whole = ctl[2 * kSortWaves + 2];
+        whole = n_whole <= cap;
+        __syncthreads();
+    }
+
     while (lo < s_hi) {
+        uint64_t hi = s_hi;
+        uint32_t n = n_whole;
+        if (!whole) {
         const uint64_t r_hi = min(s_hi, lo + ((uint64_t)kCoarseBins << sh));
         const uint32_t nbins = (uint32_t)((r_hi - lo + (1ull << sh) - 1) >> sh);
         // 1. coarse histogram of the keys in [lo, r_hi)
@@ -121,7 +208,7 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
             int i = 0;
             for (int64_t w = tid; w < x; w += kHashThreads) {
                 const uint64_t key = window_key<A, K>(a, st, pos, w, i);
-                if (key >= lo && key < r_hi) atomicAdd(hist + (uint32_t)((key - lo) >> sh), 1u);
+                if (key >= lo && key < r_hi && marked(key)) atomicAdd(hist + (uint32_t)((key - lo) >> sh), 1u);
             }
         }
         __syncthreads();
@@ -140,7 +227,7 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 run += c[q];
-                if (run > (uint32_t)kSortCap) {
+                if (run > cap) {
                     atomicMin(ctl + 2 * kSortWaves, (uint32_t)(tid * kPer + q));
                     break;
                 }
@@ -162,7 +249,7 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
             if (tid * kPer < take && (tid + 1) * kPer >= take) ctl[2 * kSortWaves + 1] = run;
         }
         __syncthreads();
-        const uint32_t n = take > 0 ? ctl[2 * kSortWaves + 1] : 0;
+        n = take > 0 ? ctl[2 * kSortWaves + 1] : 0;
         const uint32_t c_first = hist[0];
         __syncthreads();
 
@@ -197,21 +284,25 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
             sh = sh0;
             continue;
         }
-        const uint64_t hi = min(r_hi, lo + ((uint64_t)take << sh));
+        hi = min(r_hi, lo + ((uint64_t)take << sh));
         if (n > 0) {
-            // 3. gather the (key, window) pairs of [lo, hi) and sort them
+            // 3. gather the (key, window) pairs of [lo, hi)
             if (tid == 0) ctl[2 * kSortWaves + 2] = 0;
             __syncthreads();
             {
                 int i = 0;
                 for (int64_t w = tid; w < x; w += kHashThreads) {
                     const uint64_t key = window_key<A, K>(a, st, pos, w, i);
-                    if (key >= lo && key < hi) {
+                    if (key >= lo && key < hi && marked(key)) {
                         const uint32_t slot = atomicAdd(ctl + 2 * kSortWaves + 2, 1u);
                         buf[slot] = (key << 32) | (uint64_t)w;
                     }
                 }
             }
+        }
+        }
+        if (n > 0) {
+            // sort the pairs
             uint32_t P = 64;
             while (P < n) P <<= 1;
             for (uint32_t q = n + tid; q < P; q += kHashThreads) buf[q] = ~0ull;
@@ -366,16 +457,27 @@ int hsort_run(HashArgs &a, int A, int32_t items, int64_t x_max, int64_t nw_max, 
               size_t ws_bytes, hipStream_t st)
 {
     if (int rc = hsort_check_k(A, a.k)) return rc;
-    const size_t lds = hsort_layout(a, x_max, nw_max, t_max);
+    size_t lds = hsort_layout(a, x_max, nw_max, t_max);
     if (!lds) return PM_ERANGE;
     if (x_max >= (int64_t)1 << 31) return fail(PM_ERANGE, "more than 2^31 windows in one instance");
-    const int64_t entries = (int64_t)items * a.nslices;
+    int64_t entries = (int64_t)items * a.nslices;
     if (entries > 0x7fffffff) return fail(PM_ERANGE, "too many trials x slices");
     if (ws_bytes < hsort_ws_bytes(entries))
         return fail(PM_EINVAL, "workspace of %zu bytes, need %zu", ws_bytes, hsort_ws_bytes(entries));
     if (((uintptr_t)ws & 7) != 0) return fail(PM_EINVAL, "workspace must be 8-byte aligned");
-    int64_t *w = static_cast<int64_t *>(ws);
     HsortArgs g{};
+    g.cap = kSortCap;
+    if (s >= 2) {
+        // filtered: as many windows per slice as a bitmap of the (halved)
+        // buffer's bits takes at one key in ten bits; never more slices
+        g.cap = kFiltCap;
+        g.filt = kFiltLog;
+        lds -= (size_t)(2 * (kSortCap - kFiltCap) - filt_words2(g.filt)) * 4;
+        const int64_t per = (int64_t)kFiltWindows * kHashThreads;
+        a.nslices = (int)std::max<int64_t>(1, std::min<int64_t>(a.nslices, (x_max + per - 1) / per));
+        entries = (int64_t)items * a.nslices;
+    }
+    int64_t *w = static_cast<int64_t *>(ws);
     g.h = a;
     g.s = s;
     g.slice_width = ((uint64_t)a.nb + a.nslices - 1) / a.nslices;
