@@ -58,7 +58,7 @@ int check_batch(const pm_batch *B, BatchInfo *info);
 // exclusive scan of n per-entry (bucket, member) totals into bases; writes the
 // grand totals to n_out and PM_STATUS_CAPACITY when they exceed the capacities.
 // With `heavy` set, also lists in order the entries with more than heavy_above
-// buckets, and their number in n_heavy.  With parts > 1 the totals of entry j
+// buckets or heavy_members members, and their number in n_heavy.  With parts > 1 the totals of entry j
 // are the sums of ne/ms[j * parts .. j * parts + parts - 1], also written to
 // ne_sum/ms_sum.
 struct TotScan {
@@ -69,10 +69,9 @@ struct TotScan {
     uint32_t *status;
     int32_t *heavy;
     int64_t *n_heavy;
-    int64_t heavy_above;
+    int64_t heavy_above, heavy_members;
     int parts;
     int64_t *ne_sum, *ms_sum;
-    int64_t *max_heavy;  // with `heavy`: the most buckets of a heavy entry (or NULL)
 };
 int launch_tot_scan(const TotScan &a, hipStream_t st);
 

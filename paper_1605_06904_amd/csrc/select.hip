@@ -10,10 +10,12 @@
 // LDS, gathers the counts of the passing keys only, scans them into bucket
 // numbers and first member slots, and places the member windows in window
 // order.  A trial of few members lists its passing windows per wave quarter
-// in LDS and places them from the lists; otherwise a stable counting sort
-// goes over the windows in chunks: per-wave counts by LDS atomics, then each
-// wave groups its passing windows by key (by ballots over the key bits when
-// many pass), every bucket keeping its next free slot per wave in LDS.
+// in LDS and places them from the lists (should a quarter overflow its list,
+// or where the key space is small, by a stable counting sort over chunks of
+// windows: per-wave counts by LDS atomics, then each wave groups its passing
+// windows by key, every bucket keeping its next free slot per wave in LDS).  A
+// trial of many members or buckets collects its members in any order in LDS
+// and ranks them within their buckets.
 #include <algorithm>
 
 #include "pm_common.h"
@@ -26,8 +28,7 @@ struct SelWs {
     int64_t *bb;      // [m] first bucket of the trial
     int64_t *mb;      // [m] first member slot of the trial
     int64_t *n_heavy; // [1] trials with more buckets than the first emit launch takes
-    int64_t *qctr;    // [4] next unit of each heavy launch (work queue heads, [0..2]), then
-                      // the most buckets of a heavy trial ([3], written by the scan)
+    int64_t *qctr;    // [4] next unit of the heavy launch (its work queue's head, [0])
     int32_t *heavy;   // [m] those trials, in order
     int64_t *nep;     // [m][parts] buckets of each part of a trial's bins (parts > 1)
     int64_t *msp;     // [m][parts] their members
@@ -85,14 +86,13 @@ struct SelArgs {
     uint32_t *status;
     SelWs ws;
     int64_t nb, cap_b, cap_m;
-    int64_t take_lo, take_hi;  // the trials a launch takes: take_lo < buckets <= take_hi
+    int64_t light;             // k_sel_emit: members of a trial it takes at most
     int32_t m;                 // trials (items)
     uint32_t s;
     int nwb;    // bitmap words, ceil(nb / 64)
     int cb;     // buckets whose cursors the LDS holds
     int parts;  // k_sel_count: workgroups per trial
-    int ranges; // k_sel_emit_heavy: bucket ranges of cb per trial at most
-    int tier;   // k_sel_emit_heavy: its work queue (ws.qctr[tier])
+    int room;   // k_sel_emit_heavy: bytes of LDS for rows and list
 };
 
 // per (trial, part of its bins): number of passing bins, their total size
@@ -182,13 +182,9 @@ __global__ void __launch_bounds__(1024) k_tot_scan(const TotScan a)
 {
     __shared__ int64_t sa[1024], sb[1024];
     __shared__ int64_t carry[3];
-    __shared__ unsigned long long hmax;
     __shared__ uint32_t hw[16];
     const int wave = threadIdx.x >> 6, lane = lane_id();
-    if (threadIdx.x == 0) {
-        carry[0] = carry[1] = carry[2] = 0;
-        hmax = 0;
-    }
+    if (threadIdx.x == 0) carry[0] = carry[1] = carry[2] = 0;
     __syncthreads();
     for (int64_t base = 0; base < a.n; base += 1024) {
         const int64_t j = base + threadIdx.x;
@@ -208,8 +204,7 @@ __global__ void __launch_bounds__(1024) k_tot_scan(const TotScan a)
         }
         sa[threadIdx.x] = ve;
         sb[threadIdx.x] = vm;
-        const bool h = a.heavy && j < a.n && ve > a.heavy_above;
-        if (h) atomicMax(&hmax, (unsigned long long)ve);
+        const bool h = a.heavy && j < a.n && (ve > a.heavy_above || vm > a.heavy_members);
         const uint64_t hb = __ballot(h);
         if (lane == 0) hw[wave] = (uint32_t)__popcll(hb);
         __syncthreads();
@@ -248,7 +243,6 @@ __global__ void __launch_bounds__(1024) k_tot_scan(const TotScan a)
         a.n_out[1] = carry[1];
         if ((carry[0] > a.cap_b || carry[1] > a.cap_m) && a.status) atomicOr(a.status, PM_STATUS_CAPACITY);
         if (a.heavy) a.n_heavy[0] = carry[2];
-        if (a.max_heavy) a.max_heavy[0] = (int64_t)hmax;
     }
 }
 
@@ -343,21 +337,16 @@ __device__ __forceinline__ uint32_t local_bucket(const uint64_t *bm, const uint3
     return wcnt[wd] + (uint32_t)__popcll(bm[wd] & ((1ull << (key & 63u)) - 1ull));
 }
 
-// Bucket records and member lists of trial j, which has ne > 0 passing keys,
-// for its buckets r0 .. r0 + cb - 1 (all of them when ne <= cb), by one
-// workgroup of four waves.  Member cursors: rows[q][bucket - r0] in LDS.  A
-// trial with more buckets than cb is taken by several workgroups, one range
-// of buckets each, every one of them reading all of the trial's windows.
-__device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint64_t *bm, uint32_t *tmp)
+// Bucket records and member lists of trial j, which has ne in 1 .. cb passing
+// keys, by one workgroup of four waves.  Member cursors: rows[q][bucket] in
+// LDS.
+__device__ void emit_trial(const SelArgs &a, int j, int64_t ne, uint64_t *bm, uint32_t *tmp)
 {
     uint32_t *wcnt = reinterpret_cast<uint32_t *>(bm + a.nwb);  // [nwb] -> buckets before the word
     uint32_t *wsz = wcnt + a.nwb;                               // [nwb] -> members before the word
     uint32_t *rows = wsz + a.nwb;                               // [4][cb]
     const int tid = threadIdx.x, wv = tid >> 6, lane = lane_id();
     const int cb = a.cb;
-    const bool whole = r0 == 0 && ne <= cb;                           // one range: every bucket
-    const uint32_t nr = (uint32_t)std::min<int64_t>(cb, ne - r0);     // the range's buckets
-    const uint32_t rlo = (uint32_t)r0, rhi = rlo + nr;
     const uint32_t *cnt = a.counts + (int64_t)j * a.nb;
     const uint64_t *bits = a.ws.bits + (int64_t)j * a.nwb;
     const int64_t bbase = a.ws.bb[j], mbase = a.ws.mb[j];
@@ -420,11 +409,10 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint
 
     // ---- bucket records in key order (a word's buckets are its set lanes),
     // and every bucket's cursor row: its first slot, then zeros; the counts of
-    // eight non-empty words with buckets in the range are read at a time
+    // eight non-empty words are read at a time
     for (int w0 = wv * 64; w0 < a.nwb; w0 += 256) {
         const int wi = w0 + lane;
-        uint64_t nz = __ballot(wi < a.nwb && bm[wi] != 0ull && wcnt[wi] < rhi &&
-                               wcnt[wi] + (uint32_t)__popcll(bm[wi]) > rlo);
+        uint64_t nz = __ballot(wi < a.nwb && bm[wi] != 0ull);
         while (nz) {
             constexpr int G = 8;
             int wd[G];
@@ -449,11 +437,10 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint
                 const uint32_t frel = wsz[w] + wave_incl_scan(c[u]) - c[u];  // first slot within the trial
                 const uint32_t bi = wcnt[w] + (uint32_t)__popcll(wb & lanemask_lt());
                 const int64_t b = bbase + bi;
-                if (set && bi >= rlo && bi < rhi) {
+                if (set) {
                     if (b < a.cap_b) a.buckets[b] = pm_bucket{(uint32_t)j, key, c[u], (uint32_t)(mbase + frel)};
-                    const uint32_t ri = bi - rlo;
-                    rows[ri] = frel;
-                    rows[cb + ri] = rows[2 * cb + ri] = rows[3 * cb + ri] = 0u;
+                    rows[bi] = frel;
+                    rows[cb + bi] = rows[2 * cb + bi] = rows[3 * cb + bi] = 0u;
                 }
             }
         }
@@ -469,7 +456,7 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint
     const int nbits = 32 - __builtin_clz(nb32 - 1u);  // key bits (|Sigma|^k >= 4)
     auto passing = [&](uint32_t key) { return key < nb32 && ((bm32[key >> 5] >> (key & 31u)) & 1u); };
 
-    if (whole && a.ws.ms[j] <= 4 * kSelListCap) {
+    if (a.ws.ms[j] <= 4 * kSelListCap) {
         // few members: each wave lists the passing windows of its quarter of
         // the trial in order (no barrier), then one wave places the four lists,
         // which together are in window order, with the buckets' cursors (row 0)
@@ -543,110 +530,6 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint
         // rows 1-3 (which the lists overwrote) cleared again
         for (int64_t bi = tid; bi < ne; bi += 256) rows[cb + bi] = rows[2 * cb + bi] = rows[3 * cb + bi] = 0u;
         __syncthreads();
-    }
-    if (!whole || ne > kSelChunk / 2) {
-        // more buckets than half a chunk's windows (two sweeps over them per
-        // chunk would cost more than the chunk), or a range of a trial with
-        // more buckets than the LDS rows hold: the windows go by quarters
-        // (wave q owns the q-th quarter) in two passes: waves 0-2 count the
-        // members of the range's buckets into rows 1-3 with LDS atomics, one
-        // sweep turns rows 0-3 into each wave's first slot, and every wave
-        // places its quarter's members of the range
-        const uint32_t lo = (uint32_t)(x * wv / 4), hi = (uint32_t)(x * (wv + 1) / 4);  // x < 2^32
-        if (wv < 3) {
-            for (uint32_t wb = lo; wb < hi; wb += 64 * kSelU) {
-                uint32_t kk[kSelU];
-#pragma unroll
-                for (int u = 0; u < kSelU; ++u) {
-                    const uint32_t w = wb + 64 * u + lane;
-                    kk[u] = w < hi ? kj[w] : 0u;
-                }
-#pragma unroll
-                for (int u = 0; u < kSelU; ++u)
-                    if (wb + 64 * u + lane < hi && passing(kk[u])) {
-                        const uint32_t ri = local_bucket(bm, wcnt, kk[u]) - rlo;
-                        if (ri < nr) atomicAdd(rows + (wv + 1) * cb + ri, 1u);
-                    }
-            }
-        }
-        __syncthreads();
-        for (uint32_t ri = tid; ri < nr; ri += 256) {
-            const uint32_t r1 = rows[ri] + rows[cb + ri];
-            const uint32_t r2 = r1 + rows[2 * cb + ri];
-            rows[cb + ri] = r1;
-            rows[2 * cb + ri] = r2;
-            rows[3 * cb + ri] += r2;
-        }
-        __syncthreads();
-        for (uint32_t wb = lo; wb < hi; wb += 64 * kSelU) {
-            uint32_t kk[kSelU], ri[kSelU];
-            uint64_t peers[kSelU];
-#pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const uint32_t w = wb + 64 * u + lane;
-                kk[u] = w < hi ? kj[w] : 0u;
-            }
-            uint32_t nflag = 0;
-#pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const uint32_t w = wb + 64 * u + lane;
-                ri[u] = 0xffffffffu;
-                if (w < hi && passing(kk[u])) ri[u] = local_bucket(bm, wcnt, kk[u]) - rlo;
-                peers[u] = __ballot(ri[u] < nr);
-                nflag += (uint32_t)__popcll(peers[u]);
-            }
-            if (nflag >= (uint32_t)(kSelBitsMin * kSelU)) {
-                // many members: the groups of all kSelU steps at once (their
-                // ballots over the key bits interleave), then one returning LDS
-                // atomic per group head, in step order (a wave's LDS operations
-                // complete in order, so a bucket's cursor advances step by step)
-                for (int b = 0; b < nbits; ++b)
-#pragma unroll
-                    for (int u = 0; u < kSelU; ++u) {
-                        const bool bit = (kk[u] >> b) & 1u;
-                        const uint64_t on = __ballot(bit);
-                        peers[u] &= bit ? on : ~on;
-                    }
-                uint32_t old[kSelU];
-                int head[kSelU];
-#pragma unroll
-                for (int u = 0; u < kSelU; ++u) {
-                    const bool f = ri[u] < nr;
-                    head[u] = f ? __ffsll((unsigned long long)peers[u]) - 1 : lane;
-                    old[u] = kNoSlot;
-                    if (f && head[u] == lane && bbase + rlo + ri[u] < a.cap_b)
-                        old[u] = atomicAdd(rows + wv * cb + ri[u], (uint32_t)__popcll(peers[u]));
-                }
-#pragma unroll
-                for (int u = 0; u < kSelU; ++u) {
-                    const uint32_t o = __shfl(old[u], head[u]);
-                    if (ri[u] < nr && o != kNoSlot) {
-                        const int64_t slot = mbase + o + (uint32_t)__popcll(peers[u] & lanemask_lt());
-                        if (slot < a.cap_m) a.members[slot] = wb + 64 * u + lane;
-                    }
-                }
-                continue;
-            }
-#pragma unroll
-            for (int u = 0; u < kSelU; ++u) {
-                const uint32_t w = wb + 64 * u + lane;
-                const bool f = ri[u] < nr;
-                if (peers[u] == 0ull) continue;
-                const Group g = group_by_key(f, kk[u], nbits);
-                uint32_t old = kNoSlot;
-                if (f && g.head == lane && bbase + rlo + ri[u] < a.cap_b) {
-                    uint32_t *r = rows + wv * cb + ri[u];
-                    old = *r;
-                    *r = old + g.n;
-                }
-                old = __shfl(old, g.head);
-                if (f && old != kNoSlot) {
-                    const int64_t slot = mbase + old + g.rank;
-                    if (slot < a.cap_m) a.members[slot] = w;
-                }
-            }
-        }
-        return;
     }
     {
         // chunks of 2048 windows, wave q owning the q-th quarter of each: rows
@@ -728,43 +611,274 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, int64_t r0, uint
     }
 }
 
-// one workgroup per trial whose buckets fit the LDS rows
+// one workgroup per trial of few members whose buckets fit the LDS rows
 __global__ void __launch_bounds__(256) k_sel_emit(const SelArgs a)
 {
     extern __shared__ __align__(16) uint64_t bm[];
     __shared__ uint32_t tmp[256];
     const int j = blockIdx.x;
-    if (j == 0 && threadIdx.x < 3) a.ws.qctr[threadIdx.x] = 0;  // the heavy launches' queues, for after this one
+    if (j == 0 && threadIdx.x == 0) a.ws.qctr[0] = 0;  // the heavy launch's queue, for after this one
     const int64_t ne = a.ws.ne[j];
-    if (ne <= a.take_lo || ne > a.take_hi) return;
-    emit_trial(a, j, ne, 0, bm, tmp);
+    if (ne == 0 || ne > a.cb || a.ws.ms[j] > a.light) return;
+    emit_trial(a, j, ne, bm, tmp);
 }
 
-// the trials with more buckets than that, listed by the scan; a fixed grid
-// of workgroups takes the (range of cb buckets, trial) units of the trials in
-// the launch's range of bucket counts from a work queue (trials differ in
-// size by an order of magnitude), range-major (so that the trials' first
-// ranges, which every trial has, come first)
-__global__ void __launch_bounds__(256) k_sel_emit_heavy(const SelArgs a)
+// Many buckets.  The placement above (stable, by grouping the lanes of a wave)
+// is a serial chain per wave, and its four cursors of every bucket leave room
+// for few waves on a CU.  Here sixteen waves take a trial and place members in
+// any order: an LDS atomic on a bucket's one cursor gives a place in a list in
+// LDS, and when the list stands, every member counts the smaller windows of
+// its bucket's piece of it, which is its rank.  A bucket holds few members (s
+// and somewhat more), so that is a handful of LDS reads, and slots are written
+// side by side.  A bucket of more than kHeavyBig members is left out of the
+// list; a wave goes through the windows for it.
+//
+// Keys, counts and first slots go by a thread per bucket, so that a trial
+// waits for its counts once, not once for every few bitmap words.  A trial
+// whose buckets or members exceed the LDS (split between rows and list by the
+// trial's members per bucket) goes by ranges of them, every one reading the
+// trial's keys again (from the caches).  LDS for two workgroups per CU where
+// the bitmap leaves it.  Bound by latencies and LDS accesses.  Measured on 6000
+// trials of uneven instances (k = 7, s = 3, 26000 windows each; most are
+// members): the former placement 2500 us, this one 880; on 2000 protein trials (k = 4, s = 3, 29430 windows, 160000 bins,
+// 1500 buckets): 1190 and 240.
+constexpr int kHeavyThreads = 1024;
+constexpr int kHeavyStatic = 3072;       // at least the launch's static LDS
+constexpr int kHeavyWaves = kHeavyThreads / 64;
+constexpr int kHeavyU = 8;               // key loads in flight per lane
+constexpr uint32_t kHeavyBig = 128;
+constexpr int kHeavyBigs = 256;          // big buckets of a range: the list's places / kHeavyBig at most
+constexpr uint32_t kNotListed = 0x80000000u;
+constexpr uint16_t kNoBucket = 0xffffu;
+
+// exclusive prefix sums of n values in place, v[n] receiving the total
+// (1024 threads)
+__device__ __forceinline__ void heavy_scan(uint32_t *v, int n, uint32_t *part)
+{
+    const int tid = threadIdx.x, wv = tid >> 6, per = (n + kHeavyThreads - 1) / kHeavyThreads;
+    const int lo = min(n, tid * per), hi = min(n, lo + per);
+    uint32_t s = 0;
+    for (int i = lo; i < hi; ++i) s += v[i];
+    const uint32_t incl = wave_incl_scan(s);
+    if (lane_id() == 63) part[wv] = incl;
+    __syncthreads();
+    uint32_t run = incl - s + wave_sum(lane_id() < wv ? part[lane_id()] : 0u);
+    for (int i = lo; i < hi; ++i) {
+        const uint32_t x = v[i];
+        v[i] = run;
+        run += x;
+    }
+    if (tid == kHeavyThreads - 1) v[n] = run;
+    __syncthreads();
+}
+
+// the last i in lo + 1 .. n with v[i] - v[lo] <= room, lo + 1 if there is none
+// (v ascending; the whole wave calls)
+__device__ __forceinline__ int heavy_reach(const uint32_t *v, int lo, int n, uint32_t room)
+{
+    const uint32_t base = v[lo];
+    if (v[n] - base <= room) return n;
+    int at = lo + 1;
+    for (int span = n - at; span > 0;) {  // the answer lies in at .. at + span
+        const int step = (span + 63) / 64, i = min(at + (lane_id() + 1) * step, n);
+        const int fit = __popcll(__ballot(v[i] - base <= room));
+        at = min(at + fit * step, n);
+        span = step - 1;
+    }
+    return at;
+}
+
+// trial j (ne passing keys); of several workgroups that share it, number `part`
+// of `parts` takes every parts-th range
+__device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, int part, int parts, uint64_t *bm)
+{
+    __shared__ uint32_t scan[kHeavyWaves];
+    __shared__ uint32_t big_key[kHeavyBigs], big_first[kHeavyBigs], n_big;
+    uint32_t *wcnt = reinterpret_cast<uint32_t *>(bm + a.nwb);  // [nwb + 1] -> buckets before the word
+    uint32_t *lds = wcnt + a.nwb + 1;                           // [room / 4]
+    // rows of 8 bytes and list places of 6, shared out by members per bucket
+    const int64_t ms = a.ws.ms[j];
+    const int rcap = (int)max((int64_t)64, min((int64_t)0xfff0, (int64_t)a.room * ne / (8 * ne + 6 * (ms + ms / 32))));
+    const uint32_t lcap = (uint32_t)((a.room - 8 * rcap - 4) / 6) & ~1u;
+    uint32_t *cur = lds;                                        // [rcap] key, then next list place
+    uint32_t *first = cur + rcap;                               // [rcap + 1] first slot within the rows' buckets
+    uint32_t *lw = first + rcap + 1;                            // [lcap] windows
+    uint16_t *lb = reinterpret_cast<uint16_t *>(lw + lcap);     // [lcap] their buckets (rows)
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
+    const uint32_t big = min(kHeavyBig, lcap);
+    const uint32_t *cnt = a.counts + (int64_t)j * a.nb;
+    const uint64_t *bits = a.ws.bits + (int64_t)j * a.nwb;
+    const int64_t bbase = a.ws.bb[j], mbase = a.ws.mb[j];
+    const pm_inst I = a.inst ? a.inst[a.item_inst[j]] : a.one;
+    const uint32_t *kj = a.keys + I.key_base + (int64_t)(j - I.first_item) * I.x;
+    const uint32_t x = (uint32_t)I.x;  // below 2^31
+
+    for (int w = tid; w < a.nwb; w += kHeavyThreads) {
+        const uint64_t b = word_in_key_order(bits[w]);
+        bm[w] = b;
+        wcnt[w] = (uint32_t)__popcll(b);
+    }
+    __syncthreads();
+    heavy_scan(wcnt, a.nwb, scan);
+
+    uint32_t m_rows = 0;  // members before the rows' buckets
+    int r = 0;
+    for (int w0 = 0, w1; w0 < a.nwb; w0 = w1) {
+        // ---- the buckets of as many words as there are rows for
+        w1 = heavy_reach(wcnt, w0, a.nwb, (uint32_t)rcap);
+        const uint32_t b0 = wcnt[w0];
+        const int n = (int)(wcnt[w1] - b0);  // at most rcap: a word has 64
+        if (n == 0) continue;
+        for (int u = tid; u < 4 * (w1 - w0); u += kHeavyThreads) {
+            const int w = w0 + (u >> 2), sh = 16 * (u & 3);
+            const uint64_t b = bm[w];
+            uint32_t at = wcnt[w] - b0 + (uint32_t)__popcll(b & ((1ull << sh) - 1ull));
+            for (uint32_t q = (uint32_t)(b >> sh) & 0xffffu; q; q &= q - 1u)
+                cur[at++] = (uint32_t)w * 64u + (uint32_t)(sh + __ffs((int)q) - 1);
+        }
+        if (tid == 0) n_big = 0;
+        __syncthreads();
+        for (int i0 = tid; i0 < n; i0 += 4 * kHeavyThreads) {
+            uint32_t c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = i0 + u * kHeavyThreads < n ? cnt[cur[i0 + u * kHeavyThreads]] : 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * kHeavyThreads < n) first[i0 + u * kHeavyThreads] = c[u];
+        }
+        __syncthreads();
+        heavy_scan(first, n, scan);
+        if (part == 0)
+            for (int i = tid; i < n; i += kHeavyThreads) {
+                const int64_t b = bbase + b0 + i;
+                const uint32_t f = first[i];
+                if (b < a.cap_b)
+                    a.buckets[b] = pm_bucket{(uint32_t)j, cur[i], first[i + 1] - f, (uint32_t)(mbase + m_rows + f)};
+            }
+        for (int i0 = 0, i1; i0 < n; i0 = i1, ++r) {
+            // ---- a range of them whose members the list takes (or one bucket)
+            i1 = heavy_reach(first, i0, n, lcap);
+            if (r % parts != part) continue;
+            const uint32_t f0 = first[i0], nm = min(first[i1] - f0, lcap);
+            for (uint32_t p = tid; p < nm; p += kHeavyThreads) lb[p] = kNoBucket;
+            for (int i = tid; i < i1; i += kHeavyThreads) {  // (the thread that read the key above)
+                if (i < i0) continue;
+                const uint32_t f = first[i], c = first[i + 1] - f;
+                const bool kept = bbase + b0 + i < a.cap_b;
+                if (kept && c > big) {
+                    const uint32_t q = atomicAdd(&n_big, 1u);
+                    if (q < (uint32_t)kHeavyBigs) {
+                        big_key[q] = cur[i];
+                        big_first[q] = f;
+                    }
+                }
+                cur[i] = kept && c <= big ? f - f0 : kNotListed;
+            }
+            __syncthreads();
+            // ---- the list: each member of the range's listed buckets
+            uint32_t nk[kHeavyU];  // the next step's keys, loaded ahead
+            auto load_keys = [&](uint32_t wb) {
+#pragma unroll
+                for (int u = 0; u < kHeavyU; ++u) {
+                    const uint32_t w = wb + kHeavyThreads * u + tid;
+                    nk[u] = w < x ? kj[w] : 0xffffffffu;
+                }
+            };
+            load_keys(0);
+            const uint32_t wn = (uint32_t)(w1 - w0), in = (uint32_t)(i1 - i0), lo = b0 + (uint32_t)i0;
+            for (uint32_t wb = 0; wb < x; wb += kHeavyThreads * kHeavyU) {
+                uint32_t kk[kHeavyU];
+#pragma unroll
+                for (int u = 0; u < kHeavyU; ++u) kk[u] = nk[u];
+                load_keys(wb + kHeavyThreads * kHeavyU);
+#pragma unroll
+                for (int u = 0; u < kHeavyU; ++u) {
+                    const uint32_t wd = kk[u] >> 6;  // 0xffffffff, where there is no window or key, is in no range
+                    if (wd - (uint32_t)w0 >= wn) continue;
+                    const uint64_t m = bm[wd];
+                    if (!((m >> (kk[u] & 63u)) & 1ull)) continue;
+                    const uint32_t i = wcnt[wd] + (uint32_t)__popcll(m & ((1ull << (kk[u] & 63u)) - 1ull)) - lo;
+                    if (i >= in) continue;
+                    const uint32_t p = atomicAdd(cur + i0 + i, 1u);
+                    if (p < lcap) {
+                        lw[p] = wb + kHeavyThreads * u + tid;
+                        lb[p] = (uint16_t)(i0 + i);
+                    }
+                }
+            }
+            __syncthreads();
+            // ---- ranks and slots
+            for (uint32_t p = tid; p < nm; p += kHeavyThreads) {
+                const uint32_t i = lb[p];
+                if (i == kNoBucket) continue;
+                const uint32_t f = first[i], w = lw[p], q0 = f - f0, q1 = min(first[i + 1] - f0, lcap);
+                uint32_t rank = 0;
+                for (uint32_t q = q0; q < q1; q += 4) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) v[k] = lw[min(q + k, q1 - 1)];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) rank += q + k < q1 && v[k] < w ? 1u : 0u;
+                }
+                const int64_t slot = mbase + m_rows + f + rank;
+                if (slot < a.cap_m) a.members[slot] = w;
+            }
+            // ---- big buckets: a wave finds a key's windows in order
+            const uint32_t nb = min(n_big, (uint32_t)kHeavyBigs);
+            for (uint32_t q = wv; q < nb; q += kHeavyWaves) {
+                const uint32_t key = big_key[q];
+                int64_t slot = mbase + m_rows + big_first[q];
+                for (uint32_t wb = 0; wb < x; wb += 64 * kHeavyU) {
+                    uint32_t kk[kHeavyU];
+#pragma unroll
+                    for (int u = 0; u < kHeavyU; ++u) {
+                        const uint32_t w = wb + 64 * u + lane;
+                        kk[u] = w < x ? kj[w] : 0xffffffffu;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kHeavyU; ++u) {
+                        const uint64_t hit = __ballot(kk[u] == key);
+                        const int64_t at = slot + __popcll(hit & lanemask_lt());
+                        if (kk[u] == key && at < a.cap_m) a.members[at] = wb + 64 * u + lane;
+                        slot += __popcll(hit);
+                    }
+                }
+            }
+            __syncthreads();
+            if (tid == 0) n_big = 0;
+            __syncthreads();
+        }
+        m_rows += first[n];
+        __syncthreads();
+    }
+}
+
+// the trials with more buckets than the rows above or more members than the
+// short lists (from where this form is the faster: 2000 trials of 1000 to 4000
+// members in at most 1024 buckets took 140 us by chunks, none here beside the
+// larger ones), listed by the scan: a
+// fixed grid of workgroups takes them from a work queue (trials differ in size
+// by an order of magnitude).  Where they are fewer than the workgroups the
+// chip holds, up to eight share a trial's ranges.
+__global__ void __launch_bounds__(kHeavyThreads, 8) k_sel_emit_heavy(const SelArgs a)
 {
     extern __shared__ __align__(16) uint64_t bm[];
-    __shared__ uint32_t tmp[256];
     __shared__ int64_t claim;
-    // bucket ranges of the largest heavy trial (at most a.ranges)
-    const int64_t rg = std::min<int64_t>(a.ranges, (a.ws.qctr[3] + a.cb - 1) / a.cb);
-    const int64_t nh = *a.ws.n_heavy, nu = nh * rg;
-    if (nu == 0) return;  // no heavy trial: no queue traffic
-    unsigned long long *q = reinterpret_cast<unsigned long long *>(a.ws.qctr + a.tier);
+    const int64_t nh = *a.ws.n_heavy;
+    if (nh == 0) return;  // no queue traffic
+    const int parts = (int)(nh >= gridDim.x ? 1 : min((int64_t)8, ((int64_t)gridDim.x + nh - 1) / nh));
+    unsigned long long *q = reinterpret_cast<unsigned long long *>(a.ws.qctr);
     for (;;) {
         if (threadIdx.x == 0) claim = (int64_t)atomicAdd(q, 1ull);
         __syncthreads();
         const int64_t un = claim;
         __syncthreads();
-        if (un >= nu) break;  // every workgroup ends here once the queue is past its end
-        const int j = a.ws.heavy[un % nh];
-        const int64_t ne = a.ws.ne[j], r0 = (un / nh) * (int64_t)a.cb;  // range-major
-        if (ne <= a.take_lo || ne > a.take_hi || r0 >= ne) continue;  // uniform over the workgroup
-        emit_trial(a, j, ne, r0, bm, tmp);
+        if (un >= nh * parts) break;  // every workgroup ends here once the queue is past its end
+        const int j = a.ws.heavy[un % nh], part = (int)(un / nh);
+        const int64_t ne = a.ws.ne[j];
+        // a trial that fits the LDS is one range
+        if (part > 0 && 8 * ne + 7 * a.ws.ms[j] + 1024 <= a.room) continue;  // uniform over the workgroup
+        emit_heavy(a, j, ne, part, parts, bm);
     }
 }
 
@@ -897,15 +1011,15 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
         hipLaunchKernelGGL(k_sel_count, dim3((unsigned)((int64_t)a.m * a.parts)), dim3(256), 0, st, a);
         PM_LAUNCHED();
     }
-    // a trial has at most min(|Sigma|^k, x / s) passing bins; the first emit
-    // launch keeps its LDS near 20 KB (eight workgroups per CU) and takes the
-    // trials whose buckets fit there, a second one with all the LDS the device
-    // gives takes the rest from a list the scan writes
+    // the first emit launch keeps its LDS near 20 KB (eight workgroups per CU)
+    // and takes the trials whose buckets fit there, a second one the rest, from
+    // a list the scan writes
     const int64_t ne_bound = std::min<int64_t>(a.nb, x_max / std::max<uint32_t>(a.s, 1u));
-    const int64_t lds_max = device_lds_bytes() - 2048;  // the emit kernels hold 1 KB of static LDS
-    const int64_t fit = (lds_max - 16 * nwb) / 16;
-    const int64_t cb_a = std::max<int64_t>(1, std::min<int64_t>(ne_bound, std::max<int64_t>(256, (20480 - 16 * nwb) / 16)));
+    const int64_t lds_max = device_lds_bytes() - kHeavyStatic;
+    const int64_t cb_a = std::max<int64_t>(
+        1, std::min<int64_t>(std::min<int64_t>(ne_bound, kSelChunk / 2), std::max<int64_t>(256, (20480 - 16 * nwb) / 16)));
     const bool heavy = a.nb > cb_a;  // counts not written by projection_hash may pass anywhere
+    a.light = heavy ? 4 * kSelListCap : INT64_MAX;
     TotScan ts{a.ws.ne, a.ws.ms, a.ws.bb, a.ws.mb, a.m, a.cap_b, a.cap_m, a.n_out, a.status};
     if (a.parts > 1) {
         ts.ne = a.ws.nep;
@@ -918,7 +1032,7 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
         ts.heavy = a.ws.heavy;
         ts.n_heavy = a.ws.n_heavy;
         ts.heavy_above = cb_a;
-        ts.max_heavy = a.ws.qctr + 3;
+        ts.heavy_members = a.light;
     }
     if (int rc = launch_tot_scan(ts, st)) return rc;
     static bool attr = false;
@@ -929,35 +1043,18 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
         (void)hipGetLastError();  // an unsupported attribute must not poison the launch check
         attr = true;
     }
-    a.take_lo = 0;
-    a.take_hi = cb_a;
     a.cb = (int)cb_a;
     hipLaunchKernelGGL(k_sel_emit, dim3(a.m), dim3(256), sel_emit_lds(nwb, cb_a), st, a);
     PM_LAUNCHED();
     if (heavy) {
-        // the heavy trials in tiers of LDS rows sized for four, two and one
-        // workgroups per CU (the fewer rows, the more workgroups hide each
-        // other's latency); the last tier also takes the trials beyond every
-        // LDS row count, as several ranges of buckets
-        int64_t lo = cb_a;
-        int tier = 0;
-        for (const int per_cu : {4, 2, 1}) {
-            int64_t cb = (lds_max / per_cu - 2048 - 16 * nwb) / 16;  // 1 KB static LDS, 1 KB headroom
-            if (per_cu == 1) cb = std::max<int64_t>(lo, std::min<int64_t>(ne_bound, fit));
-            else if (cb <= lo) continue;
-            cb = std::min<int64_t>(cb, std::max<int64_t>(lo, ne_bound));
-            a.cb = (int)cb;
-            a.take_lo = lo;
-            a.take_hi = per_cu == 1 ? INT64_MAX : cb;
-            // only the last tier has trials with more buckets than its rows
-            a.ranges = per_cu == 1 ? (int)((std::max<int64_t>(ne_bound, cb) + cb - 1) / cb) : 1;
-            a.tier = tier++;
-            const int grid = std::min<int32_t>(a.m, 1024);
-            hipLaunchKernelGGL(k_sel_emit_heavy, dim3(grid), dim3(256), sel_emit_lds(nwb, cb), st, a);
-            PM_LAUNCHED();
-            lo = cb;
-            if (lo >= ne_bound) break;  // no trial has more buckets
-        }
+        // two workgroups per CU while the bitmap and its scan leave them a
+        // third of their LDS
+        const int64_t half = (device_lds_bytes() / 2 - kHeavyStatic) & ~(int64_t)7;
+        const int64_t lds = half - 12 * nwb >= half / 3 ? half : lds_max & ~(int64_t)7;
+        a.room = (int)(lds - 12 * nwb - 8);
+        const int grid = (int)std::min<int64_t>(8 * (int64_t)a.m, lds == half ? 512 : 256);
+        hipLaunchKernelGGL(k_sel_emit_heavy, dim3(grid), dim3(kHeavyThreads), (size_t)lds, st, a);
+        PM_LAUNCHED();
     }
     return PM_OK;
 }
