@@ -319,12 +319,28 @@ static int check_em_args(int A, int64_t B, int32_t iters, double beta, int32_t p
     return PM_OK;
 }
 
-static int vec_launch(EmArgs &a, int A, int32_t precision, int64_t nw_max, int t_max, hipStream_t st)
+// tiled: the tiled form may take the call
+static int vec_launch(EmArgs &a, int A, int32_t precision, int64_t nw_max, int t_max, hipStream_t st, bool tiled)
 {
     a.seq_cap = nw_max * 4 <= 48 * 1024 ? (int)nw_max : 0;
     a.off_cap = (t_max + 1) * 8 <= 8 * 1024 ? t_max + 1 : 0;
     const size_t lds = ((a.seq_cap + 1) & ~1) * 4 + (size_t)a.off_cap * 8;
-    if (A == 4) return launch_em_dna(a, precision == PM_FP64, lds, st);
+    if (A == 4) {
+        // The tiled form: all lanes look at one window, counts
+        // in registers (l <= 24) and the input's codes in LDS beside its
+        // tables.  A full round measures 0.46 to 0.50 of the other form's time
+        // (OOPS and ZOOPS) and 0.55 to 0.66 (TCM).
+        a.fp32 = precision == PM_FP32;
+        a.tile_pct = tiled && a.l <= 24 && a.one.n_total <= 48 * 1024 ? (a.model == PM_TCM ? 70 : 55) : 0;
+        // with the number of models on the device both forms are launched, and
+        // the one that does not take the call ends at once
+        const bool takes = a.n_dev ? a.tile_pct && a.B * 100 >= kTileRound * a.tile_pct : tile_takes(a.B, a.tile_pct);
+        if (takes) {
+            const int rc = a.model == PM_TCM ? launch_em_tile_tcm(a, st) : launch_em_tile(a, st);
+            if (rc != PM_OK || !a.n_dev) return rc;
+        }
+        return launch_em_dna(a, precision == PM_FP64, lds, st);
+    }
     return precision == PM_FP64 ? launch_em<double>(a, lds, st) : launch_em<float>(a, lds, st);
 }
 
@@ -336,10 +352,10 @@ extern "C" size_t pm_em_workspace(const pm_seqs *S, int32_t l, int32_t precision
     return em_tables_workspace(S, l);
 }
 
-extern "C" int em_refine(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
-                         const int64_t *n_dev, int32_t iters, double beta, int32_t precision,
-                         double *theta_out, double *J_out, double *llr_out, int32_t *sites_out,
-                         void *ws, size_t ws_bytes, void *stream)
+static int refine_oops(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
+                       const int64_t *n_dev, int32_t iters, double beta, int32_t precision, double *theta_out,
+                       double *J_out, double *llr_out, int32_t *sites_out, void *ws, size_t ws_bytes, void *stream,
+                       bool tiled)
 {
     clear_error();
     int rc = check_seqs(S, l);
@@ -366,7 +382,26 @@ extern "C" int em_refine(const pm_seqs *S, int32_t l, const double *theta0, cons
     a.iters = iters;
     a.site_stride = S->t;
     a.beta = beta;
-    return vec_launch(a, S->alphabet, precision, pm_packed_words(S->alphabet, S->n_total), S->t, st);
+    return vec_launch(a, S->alphabet, precision, pm_packed_words(S->alphabet, S->n_total), S->t, st, tiled);
+}
+
+extern "C" int em_refine(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
+                         const int64_t *n_dev, int32_t iters, double beta, int32_t precision,
+                         double *theta_out, double *J_out, double *llr_out, int32_t *sites_out,
+                         void *ws, size_t ws_bytes, void *stream)
+{
+    return refine_oops(S, l, theta0, bg, B, n_dev, iters, beta, precision, theta_out, J_out, llr_out, sites_out, ws,
+                       ws_bytes, stream, true);
+}
+
+// em_refine in the batch's form, whatever the number of models: a problem
+// gives the same answer alone, in a batch and in ranges of its trials
+int pm::em_refine_as_batch(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
+                           const int64_t *n_dev, int32_t iters, double beta, int32_t precision, double *theta_out,
+                           double *J_out, double *llr_out, int32_t *sites_out, void *ws, size_t ws_bytes, void *stream)
+{
+    return refine_oops(S, l, theta0, bg, B, n_dev, iters, beta, precision, theta_out, J_out, llr_out, sites_out, ws,
+                       ws_bytes, stream, false);
 }
 
 extern "C" int em_refine_model(const pm_seqs *S, int32_t l, int32_t model, double mix0, const double *theta0,
@@ -403,7 +438,8 @@ extern "C" int em_refine_model(const pm_seqs *S, int32_t l, int32_t model, doubl
     a.model = model;
     a.mix0 = mix0;
     a.mix_out = mix_out;
-    return vec_launch(a, S->alphabet, precision, pm_packed_words(S->alphabet, S->n_total), S->t, as_stream(stream));
+    return vec_launch(a, S->alphabet, precision, pm_packed_words(S->alphabet, S->n_total), S->t, as_stream(stream),
+                      true);
 }
 
 extern "C" size_t pm_em_batch_workspace(const pm_batch *B, int32_t precision)
@@ -482,7 +518,7 @@ extern "C" int em_refine_batch(const pm_batch *Bt, const pm_bucket *buckets, con
     a.iters = iters;
     a.site_stride = info.t_max;
     a.beta = beta;
-    return vec_launch(a, Bt->alphabet, precision, info.nw_max, info.t_max, st);
+    return vec_launch(a, Bt->alphabet, precision, info.nw_max, info.t_max, st, false);
 }
 
 extern "C" int em_best(const double *J, int64_t B, const int64_t *n_dev, int32_t iters, const double *theta,

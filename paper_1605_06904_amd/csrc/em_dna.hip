@@ -22,6 +22,8 @@
 // registers, the log-sum-exp is formed against its largest score, and the
 // same exponentials, times one factor per sequence, are the posteriors.
 // Longer sequences are scored twice.
+#include <algorithm>
+
 #include "dna3.h"
 #include "em_vec.h"
 
@@ -68,7 +70,7 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
     const int64_t b = blockIdx.x;
     int64_t nvalid = a.n_dev ? *a.n_dev : a.B;
     if (nvalid > a.B) nvalid = a.B;
-    if (b >= nvalid) return;
+    if (b >= nvalid || tile_takes(nvalid, a.tile_pct)) return;
 
     __shared__ double th[4 * 32];
     __shared__ T wt[4 * 32];                 // log-odds of every letter and position
@@ -313,7 +315,16 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
 template <typename T, int NG>
 static void launch_model(const EmArgs &a, size_t lds, hipStream_t st)
 {
-    const dim3 grid((unsigned)a.B), block(kEmThreads);
+    // the largest number of models that is this form's (tile_takes)
+    int64_t most = a.B;
+    if (tile_takes(a.B, a.tile_pct)) {
+        most = 1;
+        for (int64_t r = 1; (r - 1) * kTileRound < a.B; ++r) {
+            const int64_t n = std::min({a.B, r * kTileRound, (r * kTileRound * a.tile_pct + 99) / 100 - 1});
+            if (n > (r - 1) * kTileRound) most = std::max(most, n);
+        }
+    }
+    const dim3 grid((unsigned)most), block(kEmThreads);
     if (a.model == PM_OOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_OOPS>), grid, block, lds, st, a);
     else if (a.model == PM_ZOOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_ZOOPS>), grid, block, lds, st, a);
     else hipLaunchKernelGGL((k_em_dna<T, NG, PM_TCM>), grid, block, lds, st, a);

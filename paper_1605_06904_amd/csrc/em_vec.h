@@ -29,7 +29,20 @@ struct EmArgs {
     double *mix_out;  // [B] mixing parameter of the final E-step, or NULL
     int seq_cap;      // LDS words reserved for the packed input (0: read from global)
     int off_cap;      // LDS offsets reserved (0: read from global)
+    int tile_pct;     // tiled form: see tile_takes (0: never)
+    int fp32;         // tiled form: sites by FP32 scores
 };
+
+// Whether the tiled form (em_tile.h) takes a call of n models: its time goes by
+// rounds of sixteen models per CU, full or not, and a full round takes pct
+// hundredths of the time that the workgroup-per-model form takes for as many
+// models.  One form takes all models of a call, so that equal models have
+// equal results.
+constexpr int64_t kTileRound = 16 * 256;
+__host__ __device__ inline bool tile_takes(int64_t n, int pct)
+{
+    return pct > 0 && (n + kTileRound - 1) / kTileRound * kTileRound * pct <= 100 * n;
+}
 
 constexpr int kEmThreads = 256;
 constexpr int kEmWaves = kEmThreads / 64;
@@ -81,5 +94,8 @@ __device__ __forceinline__ int64_t wave_min_i64(int64_t v)
 
 // the DNA form (em_dna.hip); a.seq_cap and a.off_cap are set, lds their bytes
 int launch_em_dna(const EmArgs &a, bool fp64, size_t lds, hipStream_t st);
+// the tiled form (em_tile.h)
+int launch_em_tile(const EmArgs &a, hipStream_t st);      // OOPS and ZOOPS
+int launch_em_tile_tcm(const EmArgs &a, hipStream_t st);
 
 }  // namespace pm

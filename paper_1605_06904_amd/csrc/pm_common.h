@@ -93,6 +93,9 @@ int select_counted(const pm_inst &one, const pm_inst *inst, const int32_t *item_
                    int64_t cap_buckets, uint32_t *members, int64_t cap_members, int64_t *n_out, void *ws,
                    uint32_t *status, int64_t x_max, hipStream_t st);
 
+int em_refine_as_batch(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
+                       const int64_t *n_dev, int32_t iters, double beta, int32_t precision, double *theta_out,
+                       double *J_out, double *llr_out, int32_t *sites_out, void *ws, size_t ws_bytes, void *stream);
 int em_refine_mfma(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
                    const int64_t *n_dev, int32_t iters, double beta, double *theta_out, double *J_out,
                    double *llr_out, int32_t *sites_out, void *ws, size_t ws_bytes, bool split, hipStream_t st);

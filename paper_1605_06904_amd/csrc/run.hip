@@ -223,7 +223,7 @@ int run_single(const Prepared &Q, const pm_options &O, pm_result &R, hipStream_t
     PM_CALL(bucket_profile(&S, l, d_bk.as<pm_bucket>(), d_mem.as<uint32_t>(), nmem, nbk, nullptr,
                            d_prof.as<uint32_t>(), st));
     PM_CALL(theta_init(A, l, d_prof.as<uint32_t>(), nbk, nullptr, d_bg.as<double>(), O.beta, d_th0.as<double>(), st));
-    PM_CALL(em_refine(&S, l, d_th0.as<double>(), d_bg.as<double>(), nbk, nullptr, O.em_iters, O.beta, O.precision,
+    PM_CALL(em_refine_as_batch(&S, l, d_th0.as<double>(), d_bg.as<double>(), nbk, nullptr, O.em_iters, O.beta, O.precision,
                       d_th.as<double>(), d_J.as<double>(), d_llr.as<double>(), d_sites.as<int32_t>(), d_emws.p, em_ws,
                       st));
     PM_CALL(em_best(d_J.as<double>(), nbk, nullptr, O.em_iters, d_th.as<double>(), A, l, d_best.as<int64_t>(),
