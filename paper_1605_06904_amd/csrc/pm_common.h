@@ -58,7 +58,8 @@ int check_batch(const pm_batch *B, BatchInfo *info);
 // exclusive scan of n per-entry (bucket, member) totals into bases; writes the
 // grand totals to n_out and PM_STATUS_CAPACITY when they exceed the capacities.
 // With `heavy` set, also lists in order the entries with more than heavy_above
-// buckets or heavy_members members, and their number in n_heavy.  With parts > 1 the totals of entry j
+// buckets, or (see heavy_members) more than heavy_members members, and their
+// number in n_heavy.  With parts > 1 the totals of entry j
 // are the sums of ne/ms[j * parts .. j * parts + parts - 1], also written to
 // ne_sum/ms_sum.
 struct TotScan {

@@ -175,6 +175,15 @@ __device__ __forceinline__ uint64_t word_in_key_order(uint64_t b)
     return spread4(b) | (spread4(b >> 16) << 1) | (spread4(b >> 32) << 2) | (spread4(b >> 48) << 3);
 }
 
+// whether a trial of few buckets has so many members that they are listed and
+// ranked; ranking takes a bucket's members times themselves, so not where
+// buckets are large (protein k = 2, 85 members a bucket: 420 us placed by
+// chunks, 1900 ranked)
+__device__ __forceinline__ bool heavy_members(int64_t buckets, int64_t members, int64_t light)
+{
+    return members > light && members <= 32 * buckets;
+}
+
 // exclusive scan of per-trial (or per trial-slice) totals, one workgroup:
 // bases of every entry, the required totals in n_out, capacity status, and
 // on request the list of heavy entries
@@ -204,7 +213,7 @@ __global__ void __launch_bounds__(1024) k_tot_scan(const TotScan a)
         }
         sa[threadIdx.x] = ve;
         sb[threadIdx.x] = vm;
-        const bool h = a.heavy && j < a.n && (ve > a.heavy_above || vm > a.heavy_members);
+        const bool h = a.heavy && j < a.n && (ve > a.heavy_above || heavy_members(ve, vm, a.heavy_members));
         const uint64_t hb = __ballot(h);
         if (lane == 0) hw[wave] = (uint32_t)__popcll(hb);
         __syncthreads();
@@ -537,6 +546,7 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, uint64_t *bm, ui
         // 0-3 into each wave's first slot, the waves place their members, and
         // wave 3's row, now the first free slot, becomes row 0 again
         // the next chunk's keys are loaded while this one is placed
+        const bool sparse = a.ws.ms[j] < x / 256;
         uint32_t nk[kSelU];
 #pragma unroll
         for (int u = 0; u < kSelU; ++u) {
@@ -564,7 +574,8 @@ __device__ void emit_trial(const SelArgs &a, int j, int64_t ne, uint64_t *bm, ui
 #pragma unroll
                 for (int u = 0; u < kSelU; ++u) fl |= 64 * u + lane < left && passing(kk[u]) ? 1u << u : 0u;
             }
-            if (!__syncthreads_or(fl != 0u)) continue;
+            // a chunk without members is passed over, where there can be some
+            if (sparse && !__syncthreads_or(fl != 0u)) continue;
             if (wv < 3) {
                 // counts only: one LDS atomic per member, no grouping
 #pragma unroll
@@ -619,7 +630,7 @@ __global__ void __launch_bounds__(256) k_sel_emit(const SelArgs a)
     const int j = blockIdx.x;
     if (j == 0 && threadIdx.x == 0) a.ws.qctr[0] = 0;  // the heavy launch's queue, for after this one
     const int64_t ne = a.ws.ne[j];
-    if (ne == 0 || ne > a.cb || a.ws.ms[j] > a.light) return;
+    if (ne == 0 || ne > a.cb || heavy_members(ne, a.ws.ms[j], a.light)) return;
     emit_trial(a, j, ne, bm, tmp);
 }
 
@@ -1018,7 +1029,8 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
     const int64_t lds_max = device_lds_bytes() - kHeavyStatic;
     const int64_t cb_a = std::max<int64_t>(
         1, std::min<int64_t>(std::min<int64_t>(ne_bound, kSelChunk / 2), std::max<int64_t>(256, (20480 - 16 * nwb) / 16)));
-    const bool heavy = a.nb > cb_a;  // counts not written by projection_hash may pass anywhere
+    // counts not written by projection_hash may pass anywhere
+    const bool heavy = a.nb > cb_a;
     a.light = heavy ? 4 * kSelListCap : INT64_MAX;
     TotScan ts{a.ws.ne, a.ws.ms, a.ws.bb, a.ws.mb, a.m, a.cap_b, a.cap_m, a.n_out, a.status};
     if (a.parts > 1) {
