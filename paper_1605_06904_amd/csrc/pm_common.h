@@ -179,16 +179,28 @@ __device__ __forceinline__ T wave_max(T v)
     return v;
 }
 
-// inclusive prefix sum over the 64 lanes (all lanes active)
+// inclusive prefix sum over the 64 lanes (all lanes active), by lane moves in
+// the vector unit (row shifts, then the last lane of each row to the next rows)
+// rather than LDS permutes
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 {
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t n = __shfl_up(v, o);
-        if (lane >= o) v += n;
-    }
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);
     return v;
+}
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
 }
 
 // v of the lane that a DPP control names, `none` in lanes that have no such
@@ -202,9 +214,7 @@ __device__ __forceinline__ double dpp_or(double v, double none)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// inclusive prefix sum of doubles over the 64 lanes, by lane moves in the
-// vector unit (row shifts, then the last lane of each row to the next rows)
-// rather than LDS permutes
+// the same of doubles
 __device__ __forceinline__ double wave_incl_sum(double v)
 {
     v += dpp_or<0x111, 0xf>(v, 0.0);
