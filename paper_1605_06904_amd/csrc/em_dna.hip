@@ -1,8 +1,9 @@
 // a7 - a9 for DNA models on the vector units: OOPS, ZOOPS and TCM EM in FP64
 // or FP32 (see em.hip for the protein form and projmotif.h for the models).
 //
-// One workgroup of four waves per model; each wave owns whole sequences and a
-// lane owns windows.  What bounds this is LDS traffic per window: scoring is
+// One workgroup of four or eight waves per model; a wave takes whole sequences
+// and a lane takes windows.  Sequences are summed by eight slots whatever the
+// waves, so that a model's result does not depend on their number.  What bounds this is LDS traffic per window: scoring is
 // a table read per position and the M-step a table update per position.
 // Both go by three letters at a time here: the E-step reads ceil(l/3) tables
 // of 64 three-letter sums (formed once per iteration from the l columns), and
@@ -29,7 +30,8 @@
 
 namespace pm {
 
-constexpr int kNC = 16;  // windows a lane holds in registers
+constexpr int kNC = 16;    // windows a lane holds in registers
+constexpr int kSlots = 8;  // sequences i, i + 8, .. are summed together
 
 // the score of a window: ceil(l/3) table reads
 template <typename T, int NG, int Q = 0>
@@ -64,9 +66,10 @@ __device__ __forceinline__ float eps<float>() { return 1.1920929e-7f; }
 template <>
 __device__ __forceinline__ double eps<double>() { return 2.220446049250313e-16; }
 
-template <typename T, int NG, int MODEL>
-__global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
+template <typename T, int NG, int MODEL, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_em_dna(const EmArgs a)
 {
+    constexpr int kThreads = 64 * WAVES;
     const int64_t b = blockIdx.x;
     int64_t nvalid = a.n_dev ? *a.n_dev : a.B;
     if (nvalid > a.B) nvalid = a.B;
@@ -75,9 +78,9 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
     __shared__ double th[4 * 32];
     __shared__ T wt[4 * 32];                 // log-odds of every letter and position
     __shared__ T W3[64 * NG];                // their sums over three positions
-    __shared__ double C3[kEmWaves][64 * NG]; // posteriors by three letters, per wave
-    __shared__ double csum[64 * NG];         // the same over the waves
-    __shared__ double red[kEmWaves];
+    __shared__ double C3[kSlots][64 * NG];   // posteriors by three letters, per slot
+    __shared__ double csum[64 * NG];         // the same over the slots
+    __shared__ double red[WAVES], llr_slot[kSlots];
     __shared__ double colsum[32];
     __shared__ double ztot;
     extern __shared__ __align__(16) uint32_t dyn[];
@@ -90,14 +93,13 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
     const double beta = a.beta;
     const int seq_words = a.seq_cap ? (int)((I.n_total + 15) / 16 + 4) : 0;
 
-    for (int i = tid; i < AL; i += kEmThreads) th[i] = a.theta0[b * AL + i];
-    for (int i = tid; i < seq_words; i += kEmThreads) seq[i] = I.packed[i];
+    for (int i = tid; i < AL; i += kThreads) th[i] = a.theta0[b * AL + i];
+    for (int i = tid; i < seq_words; i += kThreads) seq[i] = I.packed[i];
     if (a.off_cap)
-        for (int i = tid; i <= t; i += kEmThreads) offs[i] = I.offsets[i];
+        for (int i = tid; i <= t; i += kThreads) offs[i] = I.offsets[i];
     __syncthreads();
     const uint32_t *W = a.seq_cap ? seq : I.packed;
     const int64_t *O = a.off_cap ? offs : I.offsets;
-    double *ac = C3[wv];
 
     // mixing parameter of ZOOPS (gamma) or TCM (lambda); OOPS has none
     double mix = a.mix0;
@@ -105,15 +107,15 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
         const bool last = it == a.iters;
         const double lmix = MODEL == PM_OOPS ? 0.0 : log(mix), lnone = MODEL == PM_OOPS ? 0.0 : log1p(-mix);
         double pr = 0;
-        for (int i = tid; i < AL; i += kEmThreads) {
+        for (int i = tid; i < AL; i += kThreads) {
             const int c = i / l;
             const double v = th[i];
             wt[i] = (T)(log(v) - log(a.bg[c]));
             if (beta != 0) pr += a.bg[c] * log(v);
         }
-        for (int i = tid; i < kEmWaves * 64 * NG; i += kEmThreads) (&C3[0][0])[i] = 0;
-        pr = block_sum(pr, red);  // includes the barrier that publishes wt
-        for (int e = tid; e < 64 * NG; e += kEmThreads) {
+        for (int i = tid; i < kSlots * 64 * NG; i += kThreads) (&C3[0][0])[i] = 0;
+        pr = block_sum<WAVES>(pr, red);  // includes the barrier that publishes wt
+        for (int e = tid; e < 64 * NG; e += kThreads) {
             const int p = e / 64 * 3;
             T v = wt[((e >> 4) & 3) * l + p];
             if (p + 1 < l) v += wt[((e >> 2) & 3) * l + p + 1];
@@ -130,156 +132,161 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
             tol = wave_sum(m) * (T)(2 * 32) * eps<T>();
         }
 
-        double llr_w = 0;
-        for (int i = wv; i < t; i += kEmWaves) {
-            const int64_t s0 = O[i];
-            const int L = (int)(O[i + 1] - s0) - l + 1;
-            if (MODEL == PM_TCM) {
-                // every window its own two-component mixture: one sweep gives
-                // its log-likelihood term, its posterior and its counts
-                const T lm = (T)lmix, ln0 = (T)lnone;
-                double lsum = 0;
-                T bv = ninf<T>();
-                int64_t ba = 0;
-                for (int x = lane; x < L; x += 64) {
-                    const Win w = load_win(W, s0 + x);
-                    const T s = score3<T, NG>(w, W3);
-                    // the larger component, and what the other is of it
-                    const T v = lm + s;
-                    const bool site = v > ln0;
-                    const T e = v == ninf<T>() ? (T)0 : ln0 == ninf<T>() ? (T)0 : ex(site ? ln0 - v : v - ln0);
-                    lsum += (double)((site ? v : ln0) + lg1p(e));
-                    if (last) {
-                        const T so = score_in_order(w, wt, l);
-                        if (so > bv) {
-                            bv = so;
-                            ba = x;
-                        }
-                        continue;
-                    }
-                    const T z = (site ? (T)1 : e) / ((T)1 + e);
-                    scatter3<NG>(w, z, ac);
-                }
-                llr_w += wave_sum(lsum);
-                if (last && a.sites) {
-                    const T bm = wave_max(bv);
-                    const int64_t cand = wave_min_i64(bv == bm ? ba : INT64_MAX);
-                    // reported when that window's posterior is at least 1/2
-                    const bool keep = (double)bm + lmix >= lnone;
-                    if (lane == 0) a.sites[b * a.site_stride + i] = keep ? (int32_t)cand : -1;
-                }
-                continue;
-            }
-            // windows past the end read the last one and score -inf
-            auto win_at = [&](int x) { return load_win(W, s0 + (x < L ? x : L - 1)); };
-            const bool held = L <= 64 * kNC;
-            T s[kNC];
-            T mx = ninf<T>();
-            double sm = 0;  // FP64 sum of exponentials in both precisions
-            if (held) {
-#pragma unroll
-                for (int c = 0; c < kNC; ++c) {
-                    s[c] = ninf<T>();
-                    if (64 * c < L) {
-                        const int x = 64 * c + lane;
-                        const T v = score3<T, NG>(win_at(x), W3);
-                        s[c] = x < L ? v : ninf<T>();
-                        mx = s[c] > mx ? s[c] : mx;
-                    }
-                }
-            } else {
-                for (int x = lane; x < L; x += 64) {
-                    const T v = score3<T, NG>(win_at(x), W3);
-                    mx = v > mx ? v : mx;
-                }
-            }
-            const T M = wave_max(mx);
-            if (held) {
-#pragma unroll
-                for (int c = 0; c < kNC; ++c)
-                    if (64 * c < L) {
-                        const T e = ex(s[c] - M);
-                        sm += s[c] > ninf<T>() ? (double)e : 0.0;
-                        if (!last) s[c] = e;
-                    }
-            } else {
-                for (int x = lane; x < L; x += 64) {
-                    const T v = score3<T, NG>(win_at(x), W3);
-                    sm += v > ninf<T>() ? (double)ex(v - M) : 0.0;
-                }
-            }
-            const double Ssum = wave_sum(sm);
-            const double lse = (double)M + log(Ssum);
-            // OOPS: LLR_i = LSE_i - ln L_i, Z = e^{s - LSE_i}.  ZOOPS: the
-            // sequence holds no site with probability 1 - gamma, so
-            // LLR_i = ln((1 - gamma) + gamma e^{LSE_i} / L_i) and
-            // Z = gamma e^s / (L_i e^{LLR_i}); q_i = sum_a Z is its site mass
-            double li, f, qi = 1.0;  // Z = f e^{s - M}
-            if (MODEL == PM_ZOOPS) {
-                const double lsite = lmix - log((double)L) + lse;
-                li = log_add(lnone, lsite);
-                qi = exp(lsite - li);
-                f = qi / Ssum;
-            } else {
-                li = lse - log((double)L);
-                f = 1.0 / Ssum;
-            }
-            llr_w += li;
-            if (last) {
-                if (a.sites) {
+        for (int slot = wv; slot < kSlots; slot += WAVES) {
+            double *ac = C3[slot];
+            double llr_w = 0;
+            for (int i = slot; i < t; i += kSlots) {
+                const int64_t s0 = O[i];
+                const int L = (int)(O[i + 1] - s0) - l + 1;
+                if (MODEL == PM_TCM) {
+                    // every window its own two-component mixture: one sweep gives
+                    // its log-likelihood term, its posterior and its counts
+                    const T lm = (T)lmix, ln0 = (T)lnone;
+                    double lsum = 0;
                     T bv = ninf<T>();
                     int64_t ba = 0;
-                    auto consider = [&](int x) {
-                        const T so = score_in_order(win_at(x), wt, l);
-                        if (so > bv) {
-                            bv = so;
-                            ba = x;
+                    for (int x = lane; x < L; x += 64) {
+                        const Win w = load_win(W, s0 + x);
+                        const T s = score3<T, NG>(w, W3);
+                        // the larger component, and what the other is of it
+                        const T v = lm + s;
+                        const bool site = v > ln0;
+                        const T e = v == ninf<T>() ? (T)0 : ln0 == ninf<T>() ? (T)0 : ex(site ? ln0 - v : v - ln0);
+                        lsum += (double)((site ? v : ln0) + lg1p(e));
+                        if (last) {
+                            const T so = score_in_order(w, wt, l);
+                            if (so > bv) {
+                                bv = so;
+                                ba = x;
+                            }
+                            continue;
                         }
-                    };
-                    if (held) {
-                        uint32_t near = 0;
-#pragma unroll
-                        for (int c = 0; c < kNC; ++c)
-                            if (64 * c + lane < L && s[c] >= M - tol) near |= 1u << c;
-                        for (; near; near &= near - 1) consider(64 * (__ffs(near) - 1) + lane);
-                    } else {
-                        for (int x = lane; x < L; x += 64)
-                            if (score3<T, NG>(win_at(x), W3) >= M - tol) consider(x);
+                        const T z = (site ? (T)1 : e) / ((T)1 + e);
+                        scatter3<NG>(w, z, ac);
                     }
-                    const T bm = wave_max(bv);
-                    const int64_t cand = wave_min_i64(bv == bm ? ba : INT64_MAX);
-                    if (lane == 0) a.sites[b * a.site_stride + i] = qi >= 0.5 ? (int32_t)cand : -1;
+                    llr_w += wave_sum(lsum);
+                    if (last && a.sites) {
+                        const T bm = wave_max(bv);
+                        const int64_t cand = wave_min_i64(bv == bm ? ba : INT64_MAX);
+                        // reported when that window's posterior is at least 1/2
+                        const bool keep = (double)bm + lmix >= lnone;
+                        if (lane == 0) a.sites[b * a.site_stride + i] = keep ? (int32_t)cand : -1;
+                    }
+                    continue;
                 }
-            } else {
-                const T fz = (T)f;
+                // windows past the end read the last one and score -inf
+                auto win_at = [&](int x) { return load_win(W, s0 + (x < L ? x : L - 1)); };
+                const bool held = L <= 64 * kNC;
+                T s[kNC];
+                T mx = ninf<T>();
+                double sm = 0;  // FP64 sum of exponentials in both precisions
+                if (held) {
+#pragma unroll
+                    for (int c = 0; c < kNC; ++c) {
+                        s[c] = ninf<T>();
+                        if (64 * c < L) {
+                            const int x = 64 * c + lane;
+                            const T v = score3<T, NG>(win_at(x), W3);
+                            s[c] = x < L ? v : ninf<T>();
+                            mx = s[c] > mx ? s[c] : mx;
+                        }
+                    }
+                } else {
+                    for (int x = lane; x < L; x += 64) {
+                        const T v = score3<T, NG>(win_at(x), W3);
+                        mx = v > mx ? v : mx;
+                    }
+                }
+                const T M = wave_max(mx);
                 if (held) {
 #pragma unroll
                     for (int c = 0; c < kNC; ++c)
-                        if (64 * c + lane < L) scatter3<NG>(load_win(W, s0 + 64 * c + lane), s[c] * fz, ac);
+                        if (64 * c < L) {
+                            const T e = ex(s[c] - M);
+                            sm += s[c] > ninf<T>() ? (double)e : 0.0;
+                            if (!last) s[c] = e;
+                        }
                 } else {
                     for (int x = lane; x < L; x += 64) {
-                        const Win w = win_at(x);
-                        scatter3<NG>(w, ex(score3<T, NG>(w, W3) - M) * fz, ac);
+                        const T v = score3<T, NG>(win_at(x), W3);
+                        sm += v > ninf<T>() ? (double)ex(v - M) : 0.0;
+                    }
+                }
+                const double Ssum = wave_sum(sm);
+                const double lse = (double)M + log(Ssum);
+                // OOPS: LLR_i = LSE_i - ln L_i, Z = e^{s - LSE_i}.  ZOOPS: the
+                // sequence holds no site with probability 1 - gamma, so
+                // LLR_i = ln((1 - gamma) + gamma e^{LSE_i} / L_i) and
+                // Z = gamma e^s / (L_i e^{LLR_i}); q_i = sum_a Z is its site mass
+                double li, f, qi = 1.0;  // Z = f e^{s - M}
+                if (MODEL == PM_ZOOPS) {
+                    const double lsite = lmix - log((double)L) + lse;
+                    li = log_add(lnone, lsite);
+                    qi = exp(lsite - li);
+                    f = qi / Ssum;
+                } else {
+                    li = lse - log((double)L);
+                    f = 1.0 / Ssum;
+                }
+                llr_w += li;
+                if (last) {
+                    if (a.sites) {
+                        T bv = ninf<T>();
+                        int64_t ba = 0;
+                        auto consider = [&](int x) {
+                            const T so = score_in_order(win_at(x), wt, l);
+                            if (so > bv) {
+                                bv = so;
+                                ba = x;
+                            }
+                        };
+                        if (held) {
+                            uint32_t near = 0;
+#pragma unroll
+                            for (int c = 0; c < kNC; ++c)
+                                if (64 * c + lane < L && s[c] >= M - tol) near |= 1u << c;
+                            for (; near; near &= near - 1) consider(64 * (__ffs(near) - 1) + lane);
+                        } else {
+                            for (int x = lane; x < L; x += 64)
+                                if (score3<T, NG>(win_at(x), W3) >= M - tol) consider(x);
+                        }
+                        const T bm = wave_max(bv);
+                        const int64_t cand = wave_min_i64(bv == bm ? ba : INT64_MAX);
+                        if (lane == 0) a.sites[b * a.site_stride + i] = qi >= 0.5 ? (int32_t)cand : -1;
+                    }
+                } else {
+                    const T fz = (T)f;
+                    if (held) {
+#pragma unroll
+                        for (int c = 0; c < kNC; ++c)
+                            if (64 * c + lane < L) scatter3<NG>(load_win(W, s0 + 64 * c + lane), s[c] * fz, ac);
+                    } else {
+                        for (int x = lane; x < L; x += 64) {
+                            const Win w = win_at(x);
+                            scatter3<NG>(w, ex(score3<T, NG>(w, W3) - M) * fz, ac);
+                        }
                     }
                 }
             }
+            if (lane == 0) llr_slot[slot] = llr_w;  // (the same in every lane)
         }
-        // every lane of a wave holds the same llr_w; count each wave once
-        const double llr = block_sum(lane == 0 ? llr_w : 0.0, red);
+        __syncthreads();
+        double llr = 0;
+        for (int w = 0; w < kSlots; ++w) llr += llr_slot[w];
         if (tid == 0) {
             a.J[b * (a.iters + 1) + it] = llr + beta * pr;
             if (a.llr) a.llr[b * (a.iters + 1) + it] = llr;
         }
         if (!last) {
-            // counts of the four waves, then of every letter and position, in FP64
-            for (int e = tid; e < 64 * NG; e += kEmThreads) {
+            // counts of the slots, then of every letter and position, in FP64
+            for (int e = tid; e < 64 * NG; e += kThreads) {
                 double cs = 0;
 #pragma unroll
-                for (int w = 0; w < kEmWaves; ++w) cs += C3[w][e];
+                for (int w = 0; w < kSlots; ++w) cs += C3[w][e];
                 csum[e] = cs;
             }
             __syncthreads();
-            for (int i = tid; i < AL; i += kEmThreads) {
+            for (int i = tid; i < AL; i += kThreads) {
                 const int c = i / l, p = i % l;
                 const int sh = 4 - 2 * (p % 3);          // the letter's field in an entry's number
                 const int rest = (1 << sh) - 1;
@@ -292,14 +299,14 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
             // theta' = (counts + beta*bg) / (t + beta); every column's counts sum
             // to t, so dividing by the column's own total is the same update and
             // keeps each column exactly on the simplex under rounding
-            for (int p = tid; p < l; p += kEmThreads) {
+            for (int p = tid; p < l; p += kThreads) {
                 double tot = 0;
                 for (int c = 0; c < 4; ++c) tot += th[c * l + p];
                 colsum[p] = tot + beta;
                 if (p == 0) ztot = tot;
             }
             __syncthreads();
-            for (int i = tid; i < AL; i += kEmThreads) th[i] = (th[i] + beta * a.bg[i / l]) / colsum[i % l];
+            for (int i = tid; i < AL; i += kThreads) th[i] = (th[i] + beta * a.bg[i / l]) / colsum[i % l];
             // the mixing parameter's update: the posterior mass (every
             // column's counts total it) over t sequences (ZOOPS) or x windows
             // (TCM), capped at 1 against rounding
@@ -308,12 +315,12 @@ __global__ void __launch_bounds__(kEmThreads, 4) k_em_dna(const EmArgs a)
             __syncthreads();
         }
     }
-    for (int i = tid; i < AL; i += kEmThreads) a.theta_out[b * AL + i] = th[i];
+    for (int i = tid; i < AL; i += kThreads) a.theta_out[b * AL + i] = th[i];
     if (tid == 0 && a.mix_out) a.mix_out[b] = mix;
 }
 
-template <typename T, int NG>
-static void launch_model(const EmArgs &a, size_t lds, hipStream_t st)
+template <typename T, int NG, int WAVES>
+static void launch_waves(const EmArgs &a, size_t lds, hipStream_t st)
 {
     // the largest number of models that is this form's (tile_takes)
     int64_t most = a.B;
@@ -324,10 +331,27 @@ static void launch_model(const EmArgs &a, size_t lds, hipStream_t st)
             if (n > (r - 1) * kTileRound) most = std::max(most, n);
         }
     }
-    const dim3 grid((unsigned)most), block(kEmThreads);
-    if (a.model == PM_OOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_OOPS>), grid, block, lds, st, a);
-    else if (a.model == PM_ZOOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_ZOOPS>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((k_em_dna<T, NG, PM_TCM>), grid, block, lds, st, a);
+    const dim3 grid((unsigned)most);
+    if (a.model == PM_OOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_OOPS, WAVES>), grid, dim3(64 * WAVES), lds, st, a);
+    else if (a.model == PM_ZOOPS) hipLaunchKernelGGL((k_em_dna<T, NG, PM_ZOOPS, WAVES>), grid, dim3(64 * WAVES), lds, st, a);
+    else hipLaunchKernelGGL((k_em_dna<T, NG, PM_TCM, WAVES>), grid, dim3(64 * WAVES), lds, st, a);
+}
+
+// Eight waves per model up to two models per CU, and where the slots' tables
+// are so large that workgroups of four would leave a CU too few waves (l > 24);
+// else four: many models keep the chip busy by themselves.  5 iterations, 20
+// sequences, four -> eight waves: 256 models of l = 13 (300 symbols) 161 -> 131
+// us, l = 18 (1000) 370 -> 313; 376 models 215 -> 198, 568 -> 541; 1000 models
+// 363 -> 387.
+template <typename T, int NG>
+static void launch_model(const EmArgs &a, size_t lds, hipStream_t st)
+{
+    if constexpr (NG > 8) {
+        launch_waves<T, NG, 8>(a, lds, st);
+    } else {
+        if (a.B <= 512) launch_waves<T, NG, 8>(a, lds, st);
+        else launch_waves<T, NG, 4>(a, lds, st);
+    }
 }
 
 template <typename T>

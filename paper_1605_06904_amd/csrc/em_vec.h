@@ -69,7 +69,7 @@ __device__ __forceinline__ T log_add(T u, T v)
     return (d > 0 ? u : v) + lg1p(ex(d > 0 ? -d : d));
 }
 
-template <typename V>
+template <int WAVES = kEmWaves, typename V>
 __device__ __forceinline__ V block_sum(V v, V *red)
 {
     v = wave_sum(v);
@@ -77,7 +77,7 @@ __device__ __forceinline__ V block_sum(V v, V *red)
     __syncthreads();
     V r = red[0];
 #pragma unroll
-    for (int w = 1; w < kEmWaves; ++w) r += red[w];
+    for (int w = 1; w < WAVES; ++w) r += red[w];
     __syncthreads();
     return r;
 }
