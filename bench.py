@@ -29,21 +29,15 @@ FP16_MFMA_PEAK = 2500.0      # TFLOP/s, MI355X dense FP16 matrix cores
 # the kernel source is the one they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
     "hash.hip": ("8544af7b0b679691", {"k_hash<4,8>": 1.705e9, "k_hash<4,9>": 14.492e9, "k_hash<20,4>": 1.517e9}),
-    "em_mfma.hip": ("ff6a29f1b25ea3d3", {
-        "k_em_mfma<5,2,true,1,1>": 0.740e9 + 0.694e9,
-        "k_em_mfma<5,2,true,2,1>": 0.699e9 + 0.705e9,
-        "k_em_mfma<5,2,true,4,1>": 0.732e9 + 0.693e9,
-        "k_em_mfma<5,2,true,1,2>": 0.745e9 + 0.723e9,
-        "k_em_mfma<5,2,true,2,2>": 0.733e9 + 0.731e9,
-        "k_em_mfma<5,2,true,4,2>": 0.763e9 + 0.742e9,
-    }),
 }
 
 
 def traffic(src, kernel):
     """HBM bytes per launch of `kernel` measured with the counters, or None when
-    the kernel's source has changed since they were taken."""
+    they were not, or the kernel's source has changed since."""
     import hashlib
+    if src not in MEASURED_TRAFFIC:
+        return None
     sha, per_kernel = MEASURED_TRAFFIC[src]
     path = os.path.join(ROOT, "paper_1605_06904_amd", "csrc", src)
     with open(path, "rb") as f:
@@ -53,16 +47,18 @@ def traffic(src, kernel):
 
 def em_issued_flops(S, l, iters, nbk, split):
     """FLOPs the matrix-core EM issues for nbk models: per 16 models and
-    32-window pair of a sequence (partial pairs padded), 2 ceil(MT/2) E-step
-    MFMAs in each of iters + 1 E-steps and MT M-step MFMAs in each of iters
-    M-steps, MT = ceil(l/4), each 16x16x32 (16 384 FLOPs), doubled by the
-    split halves except the last E-step k-block when MT is odd (its hi and
-    lo halves share one MFMA); models padded to groups of 16."""
+    32-window pair of a sequence (partial pairs padded), in each of iters + 1
+    E-steps two tiles of sparse instructions (16 positions each, counted as the
+    16 384 FLOPs of the products they form), one per fragment of 16 positions,
+    and in each of iters M-steps MT dense 16x16x32 ones, MT = ceil(l/4), doubled
+    by the split halves except an E-step fragment of at most 8 positions (its hi
+    and lo halves share one instruction); models padded to groups of 16."""
     mt = (l + 3) // 4
-    lb = (mt + 1) // 2
+    frags = (mt + 3) // 4
+    shared = 1 if mt % 4 in (1, 2) else 0
     pairs = sum((n - l + 1 + 31) // 32 for n in S.lens)
     groups = (nbk + 15) // 16
-    e_step = 2 * (2 * lb - (mt & 1)) if split else 2 * lb
+    e_step = 2 * (2 * frags - shared) if split else 2 * frags
     m_step = mt * (2 if split else 1)
     per_pair = e_step * (iters + 1) + m_step * iters
     return float(groups) * pairs * per_pair * 16384.0
@@ -203,7 +199,7 @@ def main():
     # 16x16x32 MFMAs (16 384 FLOPs each), twice over in the split form
     em_mfma = em_issued_flops(S, l, iters, nbk, split=True)
     em_mfma_tfs = em_mfma / (stage["em"] / 1e3) / 1e12
-    em_kernel = f"k_em_mfma<{(l + 3) // 4},2,true,{shape_ppb},{shape_g}>"
+    em_kernel = f"k_em_mfma<{(l + 3) // 4},2,true,{shape_ppb},{shape_g},false>"
     dominant = max(stage, key=stage.get)
     if dominant == "hash+select":
         roof = {"kernel": "k_hash<4,8>", "bound": "hbm", "achieved": round(hash_gbs, 2), "peak": HBM_PEAK_GBS,

@@ -5,7 +5,7 @@
 // does not write the steps down.  The model here is the standard OOPS EM with
 // a uniform start prior and a fixed background (see projmotif.h).
 //
-// Vector path (protein here; DNA in em_dna.hip): one workgroup (4 waves) per model.  The packed instance is
+// Vector path (protein here; DNA in em_dna.h): one workgroup (4 waves) per model.  The packed instance is
 // staged in LDS; each wave owns whole sequences, so the per-sequence
 // log-sum-exp is a wavefront reduction; the E-step reads the log-odds table
 // from LDS; M-step counts go to per-wave LDS accumulators.
@@ -339,7 +339,15 @@ static int vec_launch(EmArgs &a, int A, int32_t precision, int64_t nw_max, int t
             const int rc = a.model == PM_TCM ? launch_em_tile_tcm(a, st) : launch_em_tile(a, st);
             if (rc != PM_OK || !a.n_dev) return rc;
         }
-        return launch_em_dna(a, precision == PM_FP64, lds, st);
+        // Eight waves per model up to two models per CU, and where the slots'
+        // tables are so large that workgroups of four would leave a CU too few
+        // waves (l > 24); else four: many models keep the chip busy by
+        // themselves.  5 iterations, 20 sequences, four -> eight waves: 256
+        // models of l = 13 (300 symbols) 161 -> 131 us, l = 18 (1000) 370 -> 313;
+        // 376 models 215 -> 198, 568 -> 541; 1000 models 363 -> 387.
+        if (a.l > 24 || a.B <= 512)
+            return precision == PM_FP64 ? launch_em_dna_f64_w8(a, lds, st) : launch_em_dna_f32_w8(a, lds, st);
+        return precision == PM_FP64 ? launch_em_dna_f64_w4(a, lds, st) : launch_em_dna_f32_w4(a, lds, st);
     }
     return precision == PM_FP64 ? launch_em<double>(a, lds, st) : launch_em<float>(a, lds, st);
 }

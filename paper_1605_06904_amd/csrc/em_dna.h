@@ -1,5 +1,6 @@
 // a7 - a9 for DNA models on the vector units: OOPS, ZOOPS and TCM EM in FP64
 // or FP32 (see em.hip for the protein form and projmotif.h for the models).
+// Included by one source per precision and number of waves.
 //
 // One workgroup of four or eight waves per model; a wave takes whole sequences
 // and a lane takes windows.  Sequences are summed by eight slots whatever the
@@ -23,6 +24,8 @@
 // registers, the log-sum-exp is formed against its largest score, and the
 // same exponentials, times one factor per sequence, are the posteriors.
 // Longer sequences are scored twice.
+#pragma once
+
 #include <algorithm>
 
 #include "dna3.h"
@@ -337,46 +340,28 @@ static void launch_waves(const EmArgs &a, size_t lds, hipStream_t st)
     else hipLaunchKernelGGL((k_em_dna<T, NG, PM_TCM, WAVES>), grid, dim3(64 * WAVES), lds, st, a);
 }
 
-// Eight waves per model up to two models per CU, and where the slots' tables
-// are so large that workgroups of four would leave a CU too few waves (l > 24);
-// else four: many models keep the chip busy by themselves.  5 iterations, 20
-// sequences, four -> eight waves: 256 models of l = 13 (300 symbols) 161 -> 131
-// us, l = 18 (1000) 370 -> 313; 376 models 215 -> 198, 568 -> 541; 1000 models
-// 363 -> 387.
-template <typename T, int NG>
-static void launch_model(const EmArgs &a, size_t lds, hipStream_t st)
-{
-    if constexpr (NG > 8) {
-        launch_waves<T, NG, 8>(a, lds, st);
-    } else {
-        if (a.B <= 512) launch_waves<T, NG, 8>(a, lds, st);
-        else launch_waves<T, NG, 4>(a, lds, st);
-    }
-}
-
-template <typename T>
-static int launch_groups(const EmArgs &a, size_t lds, hipStream_t st)
+// the kernel for l positions; four waves only up to eight tables (launch_em_dna)
+template <typename T, int WAVES>
+static int launch_positions(const EmArgs &a, size_t lds, hipStream_t st)
 {
     switch ((a.l + 2) / 3) {
-    case 1: launch_model<T, 1>(a, lds, st); break;
-    case 2: launch_model<T, 2>(a, lds, st); break;
-    case 3: launch_model<T, 3>(a, lds, st); break;
-    case 4: launch_model<T, 4>(a, lds, st); break;
-    case 5: launch_model<T, 5>(a, lds, st); break;
-    case 6: launch_model<T, 6>(a, lds, st); break;
-    case 7: launch_model<T, 7>(a, lds, st); break;
-    case 8: launch_model<T, 8>(a, lds, st); break;
-    case 9: launch_model<T, 9>(a, lds, st); break;
-    case 10: launch_model<T, 10>(a, lds, st); break;
-    default: launch_model<T, 11>(a, lds, st); break;
+    case 1: launch_waves<T, 1, WAVES>(a, lds, st); break;
+    case 2: launch_waves<T, 2, WAVES>(a, lds, st); break;
+    case 3: launch_waves<T, 3, WAVES>(a, lds, st); break;
+    case 4: launch_waves<T, 4, WAVES>(a, lds, st); break;
+    case 5: launch_waves<T, 5, WAVES>(a, lds, st); break;
+    case 6: launch_waves<T, 6, WAVES>(a, lds, st); break;
+    case 7: launch_waves<T, 7, WAVES>(a, lds, st); break;
+    case 8: launch_waves<T, 8, WAVES>(a, lds, st); break;
+    default:
+        if constexpr (WAVES == 8) {
+            if (a.l <= 27) launch_waves<T, 9, WAVES>(a, lds, st);
+            else if (a.l <= 30) launch_waves<T, 10, WAVES>(a, lds, st);
+            else launch_waves<T, 11, WAVES>(a, lds, st);
+        }
     }
     PM_LAUNCHED();
     return PM_OK;
-}
-
-int launch_em_dna(const EmArgs &a, bool fp64, size_t lds, hipStream_t st)
-{
-    return fp64 ? launch_groups<double>(a, lds, st) : launch_groups<float>(a, lds, st);
 }
 
 }  // namespace pm

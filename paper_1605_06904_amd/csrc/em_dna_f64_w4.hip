@@ -1,0 +1,6 @@
+// EM of DNA models with a workgroup per model: FP64, four waves.
+#include "em_dna.h"
+
+namespace pm {
+int launch_em_dna_f64_w4(const EmArgs &a, size_t lds, hipStream_t st) { return launch_positions<double, 4>(a, lds, st); }
+}  // namespace pm

@@ -2,7 +2,7 @@
 // of sixteen models at a time, the M-step on the FP64 matrix instructions.
 // Included by one source per sequence model.
 //
-// em_dna.hip gives a model a workgroup, and its time goes to LDS updates of 64
+// em_dna.h gives a model a workgroup, and its time goes to LDS updates of 64
 // lanes that meet on the same entries of a table.  Here a workgroup holds the
 // tables of sixteen models, a wave takes four windows of a sequence at once,
 // and lane 16 g + m looks at window g for model m:

@@ -92,8 +92,12 @@ __device__ __forceinline__ int64_t wave_min_i64(int64_t v)
     return v;
 }
 
-// the DNA form (em_dna.hip); a.seq_cap and a.off_cap are set, lds their bytes
-int launch_em_dna(const EmArgs &a, bool fp64, size_t lds, hipStream_t st);
+// the DNA form (em_dna.h) of four and eight waves (four: l <= 24); a.seq_cap and
+// a.off_cap are set, lds their bytes
+int launch_em_dna_f64_w4(const EmArgs &a, size_t lds, hipStream_t st);
+int launch_em_dna_f64_w8(const EmArgs &a, size_t lds, hipStream_t st);
+int launch_em_dna_f32_w4(const EmArgs &a, size_t lds, hipStream_t st);
+int launch_em_dna_f32_w8(const EmArgs &a, size_t lds, hipStream_t st);
 // the tiled form (em_tile.h)
 int launch_em_tile(const EmArgs &a, hipStream_t st);      // OOPS and ZOOPS
 int launch_em_tile_tcm(const EmArgs &a, hipStream_t st);
