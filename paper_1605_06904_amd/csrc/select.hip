@@ -672,8 +672,8 @@ __global__ void __launch_bounds__(256) k_sel_emit(const SelArgs a)
 // trial's keys again (from the caches).  LDS for two workgroups per CU where
 // the bitmap leaves it.  Bound by latencies and LDS accesses.  Measured on 6000
 // trials of uneven instances (k = 7, s = 3, 26000 windows each; most are
-// members): the former placement 2500 us, this one 880; on 2000 protein trials (k = 4, s = 3, 29430 windows, 160000 bins,
-// 1500 buckets): 1190 and 240.
+// members): 2320 us placed by groups, 730 so; on 2000 protein trials (k = 4, s = 3, 29430 windows, 160000 bins,
+// 1500 buckets): 1190 and 214.
 constexpr int kHeavyThreads = 1024;
 constexpr int kHeavyStatic = 3072;       // at least the launch's static LDS
 constexpr int kHeavyWaves = kHeavyThreads / 64;
@@ -886,9 +886,8 @@ __device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, 
 }
 
 // the trials with more buckets than the rows above or more members than the
-// short lists (from where this form is the faster: 2000 trials of 1000 to 4000
-// members in at most 1024 buckets took 140 us by chunks, none here beside the
-// larger ones), listed by the scan: a
+// short lists (on an uneven batch such trials took 140 us placed by chunks, and
+// cost nothing to be seen among the others here), listed by the scan: a
 // fixed grid of workgroups takes them from a work queue (trials differ in size
 // by an order of magnitude).  Where they are fewer than the workgroups the
 // chip holds, up to eight share a trial's ranges.
