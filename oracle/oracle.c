@@ -467,7 +467,9 @@ double or_estep_model(int model, double mix, int t, const int64_t *off, const ui
             for (int64_t a = 0; a < L; ++a)
                 if (s[w0 + a] > mx) mx = s[w0 + a];
             double sum = 0;
-            for (int64_t a = 0; a < L; ++a) sum += exp(s[w0 + a] - mx);
+            /* no window of positive probability: mx = -inf and the sum is 0 */
+            for (int64_t a = 0; a < L; ++a)
+                if (s[w0 + a] != -INFINITY) sum += exp(s[w0 + a] - mx);
             const double lsite = lmix - log((double)L) + mx + log(sum);
             const double li = log_add(lnone, lsite);
             for (int64_t a = 0; a < L; ++a) Z[w0 + a] = exp(lmix - log((double)L) + s[w0 + a] - li);

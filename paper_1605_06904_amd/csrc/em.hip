@@ -187,16 +187,17 @@ __global__ void __launch_bounds__(kEmThreads, 3) k_em_vec(const EmArgs a)
                 bv = mx;
             }
             const T M = wave_max(mx);
+            const T Mr = M > ninf<T>() ? M : (T)0;  // no finite score: every term is 0, not NaN
             if (held) {
 #pragma unroll
                 for (int c = 0; c < kHeld; ++c)
                     if (64 * c < L) {
-                        const T e = ex(s[c] - M);
+                        const T e = ex(s[c] - Mr);
                         sm += s[c] > ninf<T>() ? (double)e : 0.0;
                         s[c] = e;
                     }
             } else {
-                sm = mx > ninf<T>() ? sm * (double)ex(mx - M) : 0.0;
+                sm = mx > ninf<T>() ? sm * (double)ex(mx - Mr) : 0.0;
             }
             const double Ssum = wave_sum(sm);
             const double lse = (double)M + log(Ssum);
@@ -204,7 +205,7 @@ __global__ void __launch_bounds__(kEmThreads, 3) k_em_vec(const EmArgs a)
             // sequence holds no site with probability 1 - gamma, so
             // LLR_i = ln((1 - gamma) + gamma e^{LSE_i} / L_i) and
             // Z = gamma e^s / (L_i e^{LLR_i}); q_i = sum_a Z is its site mass
-            double li, qi = 1.0;  // Z = (qi / Ssum) e^{s - M}
+            double li, qi = 1.0;  // Z = (qi / Ssum) e^{s - Mr}; no finite score of a ZOOPS sequence: qi = 0 and no counts
             if (a.model == PM_ZOOPS) {
                 const double lsite = lmix - log((double)L) + lse;
                 li = log_add(lnone, lsite);
@@ -220,14 +221,14 @@ __global__ void __launch_bounds__(kEmThreads, 3) k_em_vec(const EmArgs a)
                     if (lane == 0) a.sites[b * a.site_stride + i] = qi >= 0.5 ? (int32_t)cand : -1;
                 }
             } else {
-                const T f = (T)(qi / Ssum);
+                const T f = (T)(a.model == PM_ZOOPS && !(Ssum > 0) ? qi : qi / Ssum);
                 if (held) {
 #pragma unroll
                     for (int c = 0; c < kHeld; ++c)
                         if (64 * c + lane < L) count_at(W, s0 + 64 * c + lane, (double)(s[c] * f), ac, l);
                 } else {
                     for (int64_t x = lane; x < L; x += 64)
-                        count_at(W, s0 + x, (double)(ex(score_at<T>(W, s0 + x, Wt, l) - M) * f), ac, l);
+                        count_at(W, s0 + x, (double)(ex(score_at<T>(W, s0 + x, Wt, l) - Mr) * f), ac, l);
                 }
             }
         }

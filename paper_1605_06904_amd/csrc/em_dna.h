@@ -201,18 +201,19 @@ __global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_e
                     }
                 }
                 const T M = wave_max(mx);
+                const T Mr = M > ninf<T>() ? M : (T)0;  // no finite score: every term is 0, not NaN
                 if (held) {
 #pragma unroll
                     for (int c = 0; c < kNC; ++c)
                         if (64 * c < L) {
-                            const T e = ex(s[c] - M);
+                            const T e = ex(s[c] - Mr);
                             sm += s[c] > ninf<T>() ? (double)e : 0.0;
                             if (!last) s[c] = e;
                         }
                 } else {
                     for (int x = lane; x < L; x += 64) {
                         const T v = score3<T, NG>(win_at(x), W3);
-                        sm += v > ninf<T>() ? (double)ex(v - M) : 0.0;
+                        sm += v > ninf<T>() ? (double)ex(v - Mr) : 0.0;
                     }
                 }
                 const double Ssum = wave_sum(sm);
@@ -221,12 +222,12 @@ __global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_e
                 // sequence holds no site with probability 1 - gamma, so
                 // LLR_i = ln((1 - gamma) + gamma e^{LSE_i} / L_i) and
                 // Z = gamma e^s / (L_i e^{LLR_i}); q_i = sum_a Z is its site mass
-                double li, f, qi = 1.0;  // Z = f e^{s - M}
+                double li, f, qi = 1.0;  // Z = f e^{s - Mr}
                 if (MODEL == PM_ZOOPS) {
                     const double lsite = lmix - log((double)L) + lse;
                     li = log_add(lnone, lsite);
                     qi = exp(lsite - li);
-                    f = qi / Ssum;
+                    f = Ssum > 0 ? qi / Ssum : qi;  // (no finite score: no counts)
                 } else {
                     li = lse - log((double)L);
                     f = 1.0 / Ssum;
@@ -266,7 +267,7 @@ __global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_e
                     } else {
                         for (int x = lane; x < L; x += 64) {
                             const Win w = win_at(x);
-                            scatter3<NG>(w, ex(score3<T, NG>(w, W3) - M) * fz, ac);
+                            scatter3<NG>(w, ex(score3<T, NG>(w, W3) - Mr) * fz, ac);
                         }
                     }
                 }

@@ -351,10 +351,10 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) k_em_tile(const EmArgs a)
                 __syncthreads();
                 for (int w = wv - w_grp; w < wv - w_grp + gw; ++w) mx = fmax(mx, part[w * M + m]);
                 __syncthreads();
-                if (low) rf = mx;
+                // no finite score: every term and the sum are 0 (the log of the sum
+                // -inf), against any finite reference
+                if (low) rf = mx > ninf<double>() ? mx : 0.0;
                 sum = sweep(rf, low);
-                // no finite score: the log-likelihood is -inf
-                if (!(rf > ninf<double>())) sum = 0;
                 __syncthreads();
             }
             if (has && w_grp == 0 && g == 0) {
@@ -373,7 +373,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) k_em_tile(const EmArgs a)
                     const double lsite = lmix - log((double)L) + rf + log(sum);
                     if (by_log) qi = exp(lsite - log_add(lnone, lsite));
                 }
-                f = qi / sum;
+                f = sum > 0 ? qi / sum : qi;  // (no finite score: no counts)
             }
             if (last) {
                 if (a.sites) {
