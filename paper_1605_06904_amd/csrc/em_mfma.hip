@@ -71,7 +71,9 @@
 // per sequence; 11.8 with the sparse E-step (16 instead of 20 MFMAs a pair),
 // 10.3 in a timing copy whose references never move.  (15,4) batch of 24
 // instances: 18.1 -> 15.4 ms; single FP16, (21,7), 16 384 models, 5 iterations:
-// 6.8 -> 6.3 ms, 3.8 ms in three parts.
+// 6.8 -> 6.3 ms, 3.8 ms in three parts.  The slots one after the other cost
+// 2 to 3% (10.4 -> 10.8 ms, 15.6 -> 15.9 ms) against one sum over all
+// sequences.
 #include <math.h>
 #include <stddef.h>
 #include <stdlib.h>
@@ -137,11 +139,14 @@ __host__ __device__ inline PlanView plan_view(const int64_t *plan, int P)
 }
 
 constexpr int kWaves = 4;  // waves (groups of 16 models) per part of a workgroup
-// A workgroup has up to three parts of kWaves waves, each taking all the
-// models but only every parts-th sequence, with its own tables and counts; the
-// parts' counts and log-likelihoods are added at the end of an iteration.  A
-// launch takes several parts (of one group of models per wave) where its
-// models alone would leave SIMDs idle: see em_parts.
+// A model's sequences are summed in em_slots slots (i, i + slots, ..), whose
+// counts and log-likelihoods are added in order at the end of an iteration: a
+// model's result does not depend on what else the launch holds.  A launch whose
+// models alone would leave SIMDs idle (em_parts) takes the slots side by side,
+// as parts of a workgroup of kWaves waves each with their own tables and
+// counts (and one group of models per wave); else they follow each other, the
+// sum of their counts waiting in theta_out, which the iteration has read and not
+// yet written.
 constexpr int kPartThreads = 64 * kWaves;
 __device__ __forceinline__ int part_thread() { return (int)(threadIdx.x % kPartThreads); }
 // tile shape 10 G + PPB: G groups of 16 models per wave, PPB window pairs
@@ -513,10 +518,18 @@ __device__ __forceinline__ void seq_slots(const EmMfmaArgs &a, int64_t tb, int i
 }
 
 // A model's log-likelihood over the sequences so far: sum of log2 references
-// and exponents, and the product of the mantissas of its sums (its logarithm
-// is taken once per iteration).
+// and exponents (multiples of 2^-23 below 2^29, so exact in any order), and the
+// product of the mantissas of its sums (its logarithm is taken once per
+// iteration).
 struct LogSum {
     double e, m;
+    // the product of another slot's mantissas multiplied in
+    __device__ __forceinline__ void join(double om)
+    {
+        const double p = om * m;
+        e += (double)__builtin_amdgcn_frexp_exp(p);
+        m = __builtin_amdgcn_frexp_mant(p);
+    }
 };
 
 // One sequence: every window pair (tables built by the whole workgroup, or
@@ -524,7 +537,8 @@ struct LogSum {
 // counts, or, in the final E-step, the best start of every model.  acc[q]:
 // the count accumulators of group q.  kSrcPre: pf holds this thread's quads of
 // the sequence's first step on entry and the first step of sequence `next` (the
-// part's next one, or its first for the next iteration) on return.
+// slot's next one, the next slot's first, or the part's first for the next
+// iteration) on return.
 //
 // mprev: this lane's slots (one per group) of the sequence's largest score in
 // the previous iteration (NULL: not kept).  The reference starts `below` under
@@ -668,15 +682,15 @@ constexpr int em_waves_per_simd()
 {
     return MT <= 5 && 3 * (em_static_lds<MT, PPB, G>() + 6 * 1024) <= 160 * 1024 ? 3 : 2;
 }
-// parts of a workgroup at most: a wave per SIMD each, as many as the registers
-// of ceil(l/4) allow
-constexpr int em_max_parts(int mt, bool split) { return mt <= 5 || (mt == 6 && !split) ? 3 : 2; }
+// slots of the sequences, and parts of a workgroup of several: a wave per SIMD
+// each, as many as the registers of ceil(l/4) allow
+constexpr int em_slots(int mt, bool split) { return mt <= 5 || (mt == 6 && !split) ? 3 : 2; }
 constexpr int kPartsPPB = 4;  // window pairs per barrier of a workgroup of several parts
 
 // G groups of 16 models per wave, kWaves waves per part; PARTS: several parts
 template <int MT, int SRC, bool SPLIT, int PPB, int G, bool PARTS>
-__global__ void __launch_bounds__((PARTS ? kPartThreads * em_max_parts(MT, SPLIT) : kPartThreads),
-                                  (PARTS ? em_max_parts(MT, SPLIT) : em_waves_per_simd<MT, PPB, G>()))
+__global__ void __launch_bounds__((PARTS ? kPartThreads * em_slots(MT, SPLIT) : kPartThreads),
+                                  (PARTS ? em_slots(MT, SPLIT) : em_waves_per_simd<MT, PPB, G>()))
 k_em_mfma(const EmMfmaArgs a0)
 {
     constexpr int NF = Tiles<MT>::NF, CX = Tiles<MT>::CX, MW = 16 * kWaves * G;
@@ -765,6 +779,8 @@ k_em_mfma(const EmMfmaArgs a0)
         idle = __builtin_amdgcn_readfirstlane(most - mine);
     }
 
+    constexpr int slots = em_slots(MT, SPLIT);
+    const int used = t < slots ? t : slots;  // those that hold sequences
     half16 Wb[G][Tiles<MT>::ops(SPLIT)];
     for (int it = 0; it <= a.iters; ++it) {
         const bool last = it == a.iters;
@@ -837,10 +853,9 @@ k_em_mfma(const EmMfmaArgs a0)
             mlow[q] = wmin - 1.0f;
         }
         LogSum ls[G];
-        bool known[G];
+        double mant[G];        // the earlier slots' mantissas
+        uint32_t lows[G] = {};  // bit 8 + k: the model was low in slot k; bit k: when the iteration was repeated for it
         const float below = it == 1 ? kBelowFirst : kBelow;
-#pragma unroll
-        for (int q = 0; q < G; ++q) known[q] = mprev && it > 0;
         for (bool again = false;; again = true) {
             // ---- clear the count accumulators (own entries)
 #pragma unroll
@@ -849,18 +864,59 @@ k_em_mfma(const EmMfmaArgs a0)
                 for (int mt = 0; mt < MT; ++mt)
                     *reinterpret_cast<float4v *>(&acc[q][r][4 * mt + g][0]) = float4v{0.f, 0.f, 0.f, 0.f};
                 ls[q] = LogSum{0.0, 1.0};
+                mant[q] = 1.0;
             }
             __syncthreads();  // tables free
-            bool low[G] = {};
-            for (int i = part; i < t; i += parts) {
+            // slot by slot (the slot of sequence i is i % slots)
+            for (int i = part, k = part; i < t;) {
+                const bool end = i + slots >= t;  // of the slot
+                const int next = !end ? i + slots : k + parts < used ? k + parts : part;
+                bool known[G], low[G] = {};
+#pragma unroll
+                for (int q = 0; q < G; ++q) known[q] = mprev && it > 0 && !((lows[q] >> k) & 1u);
                 int16_t *mp = mprev ? mprev + (int64_t)i * MW : nullptr;
-                const int next = i + parts < t ? i + parts : part;
                 if (last)
                     sweep<MT, SRC, true, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, next, acc, Wb,
                                                         mlow, mp, known, below, again, low, ls);
                 else
                     sweep<MT, SRC, false, SPLIT, PPB, G>(a, W, lutp, i, bw, nvalid, tabs, parity, tb, pf, next, acc, Wb,
                                                          mlow, mp, known, below, again, low, ls);
+#pragma unroll
+                for (int q = 0; q < G; ++q) lows[q] |= low[q] ? 256u << k : 0u;
+                i = next;
+                if (!end) continue;
+                if (PARTS || k + 1 >= used) break;
+                // ---- this slot's counts (own entries), added to the earlier ones',
+                // wait where their column of theta will be; the next slot's start
+                // from zero
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    const double em = ls[q].m;
+                    ls[q].m = mant[q];
+                    ls[q].join(em);
+                    mant[q] = ls[q].m;
+                    ls[q].m = 1.0;
+                }
+                if (!last) {
+                    // (addresses formed on the spot, from an opaque thread number,
+                    // rather than kept in registers that the sweeps need)
+                    int u = part_thread();
+                    asm volatile("" : "+v"(u));
+                    #pragma unroll 1
+                    for (int j = 0; j < MT * G; ++j) {
+                        const int q = j / MT, p = 4 * (j % MT) + u % 64 / 16;
+                        const int64_t b = b0 + u / 64 * (16 * G) + 16 * q + u % 16;
+                        float4v *own = reinterpret_cast<float4v *>(&accs[u / 64][q][u % 16][p][0]);
+                        if (p < l && b < nvalid) {
+                            double *wait = a.theta_out + b * AL + p;
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                wait[c * l] = (double)(k > 0 ? (float)wait[c * l] + (*own)[c] : (*own)[c]);
+                        }
+                        *own = float4v{0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+                ++k;
             }
             for (int k = 0; k < idle; ++k) __syncthreads();
             // repeated at most once: the low models then start from their lowest score
@@ -868,10 +924,16 @@ k_em_mfma(const EmMfmaArgs a0)
             bool any = false;
 #pragma unroll
             for (int q = 0; q < G; ++q) {
-                any |= low[q];
-                known[q] = !low[q];
+                any |= lows[q] != 0u;
+                lows[q] >>= 8;
             }
             if (!__syncthreads_or(any)) break;
+        }
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const double em = ls[q].m;
+            ls[q].m = mant[q];
+            ls[q].join(em);
         }
         // the parts' log-likelihoods, added in order (through the tables' LDS,
         // which nobody reads any more after the barrier)
@@ -883,9 +945,8 @@ k_em_mfma(const EmMfmaArgs a0)
             ls[0] = LogSum{0.0, 1.0};
             for (int q = 0; q < parts; ++q) {
                 const LogSum o = comb[q * MW + 16 * wv + r];
-                const double m = o.m * ls[0].m;
-                ls[0].e += o.e + (double)__builtin_amdgcn_frexp_exp(m);
-                ls[0].m = __builtin_amdgcn_frexp_mant(m);
+                ls[0].e += o.e;
+                ls[0].join(o.m);
             }
         }
         double llr[G];
@@ -910,6 +971,9 @@ k_em_mfma(const EmMfmaArgs a0)
                         float4v cn = *reinterpret_cast<const float4v *>(&acc_of(0)[wv][q][r][p][0]);
                         for (int k = 1; k < parts; ++k)
                             cn += *reinterpret_cast<const float4v *>(&acc_of(k)[wv][q][r][p][0]);
+                        if (!PARTS && used > 1)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) cn[c] = (float)a.theta_out[b * AL + c * l + p] + cn[c];
                         // every column's counts sum to t: normalising by the column's
                         // own total is the same update and stays on the simplex
                         const double tot = (double)cn[0] + (double)cn[1] + (double)cn[2] + (double)cn[3] + beta;
@@ -1028,18 +1092,16 @@ static int prepare_tables(EmMfmaArgs &a, const pm_seqs *S, int l, void *ws, size
 
 constexpr int kCUs = 256;
 
-// Parts of a launch's workgroups: as many as leave every CU's wave slots
-// filled, by the workgroups of 64 models alone (in every tile shape, so that
-// results do not depend on the shape).  16 384 models of the (21,7) workload
-// in single FP16, one workgroup per CU: 6.3 ms in one part, 4.3 in two, 3.8 in
-// three.
+// Parts of a launch's workgroups: the slots side by side where every CU has a
+// workgroup of 64 models at most, else one.  16 384 models of the (21,7)
+// workload in single FP16, one workgroup per CU: 6.3 ms in one part, 3.8 in
+// three; just above (16 500 to 24 500 models, 3 iterations) 5.7 ms in one part
+// against 6.1 in two, and on (18,6) in split FP16 1.55 against 1.65.
 static int em_parts(const EmMfmaArgs &a)
 {
-    const int most = em_max_parts((a.l + 3) / 4, a.split != 0);
-    const int64_t groups = em_groups(a, 16 * kWaves);
-    int64_t n = (int64_t)most * kCUs / (groups > 0 ? groups : 1);
-    if (n > a.site_stride) n = a.site_stride;
-    return n < 1 ? 1 : n > most ? most : (int)n;
+    const int slots = em_slots((a.l + 3) / 4, a.split != 0);
+    if (em_groups(a, 16 * kWaves) > kCUs) return 1;
+    return a.site_stride < slots ? a.site_stride : slots;
 }
 
 template <int MT, bool SPLIT, int PPB, int G, bool PARTS = false>
