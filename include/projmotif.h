@@ -343,7 +343,11 @@ size_t pm_em_workspace(const pm_seqs *S, int32_t l, int32_t precision);
  * l <= 24), PPB window pairs whose one-hot tables are staged per workgroup
  * barrier (1, 2 or 4).  Pass B of the size the later calls will have: the
  * shapes differ in workgroup size, so their ranking depends on how well B
- * fills the device.
+ * fills the device.  Calls whose models fill at most one workgroup of 64 per
+ * CU (256 of them; a batch counts one more per instance) run in a form of
+ * their own, several parts of the sequences at a time, whatever the tuned
+ * shape, unless em_set_tuning has set one; every form and shape gives the same
+ * results, bit for bit.
  * theta_out, J_out: device scratch of em_refine's shapes (overwritten);
  * ws, ws_bytes: as for em_refine (pass the workspace the timed calls will
  * have).  DNA only.  choice_out: host int32[1] or NULL.  em_tuning returns
@@ -354,7 +358,8 @@ int em_autotune(const pm_seqs *S, int32_t l, const double *theta0, const double 
 int em_tuning(int32_t l, int32_t precision);
 /* Records `shape` (coded as above) for l's length class and `precision`, in
  * place of a tuned or default one: for callers that tuned in an earlier
- * process or want a fixed shape.  PM_EINVAL for a shape the class cannot
+ * process or want a fixed shape.  Every later call of the class runs in it,
+ * until em_autotune records another.  PM_EINVAL for a shape the class cannot
  * take. */
 int em_set_tuning(int32_t l, int32_t precision, int32_t shape);
 

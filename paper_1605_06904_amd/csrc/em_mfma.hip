@@ -152,6 +152,10 @@ __device__ __forceinline__ int part_thread() { return (int)(threadIdx.x % kPartT
 // tile shape 10 G + PPB: G groups of 16 models per wave, PPB window pairs
 // built per workgroup barrier
 constexpr int kShapeDefault = 14;  // untuned
+// the form in parts: one group of models per wave, kPartsPPB window pairs
+constexpr int kPartsPPB = 4;
+constexpr int kShapeParts = 100 + 10 + kPartsPPB;
+constexpr int shape_groups(int shape) { return shape / 10 % 10; }
 constexpr int kMaxMT2 = 6;         // G = 2 for ceil(l/4) <= 6 (registers)
 constexpr float kPOff = 3.0f;
 constexpr float kSlack = 12.0f;
@@ -685,7 +689,6 @@ constexpr int em_waves_per_simd()
 // slots of the sequences, and parts of a workgroup of several: a wave per SIMD
 // each, as many as the registers of ceil(l/4) allow
 constexpr int em_slots(int mt, bool split) { return mt <= 5 || (mt == 6 && !split) ? 3 : 2; }
-constexpr int kPartsPPB = 4;  // window pairs per barrier of a workgroup of several parts
 
 // G groups of 16 models per wave, kWaves waves per part; PARTS: several parts
 template <int MT, int SRC, bool SPLIT, int PPB, int G, bool PARTS>
@@ -1110,7 +1113,7 @@ static int launch_em_mfma(const EmMfmaArgs &a, hipStream_t st)
     const int64_t groups = em_groups(a, 16 * kWaves * G);
     EmMfmaArgs b = a;
     b.mcap = a.site_stride < kPrevT ? a.site_stride : kPrevT;  // site_stride: the most sequences of an instance
-    const int parts = PARTS ? em_parts(a) : 1;
+    const int parts = PARTS ? em_parts(a) : 1;  // (PARTS: launch_shape has seen more than one)
     const size_t lds = (size_t)parts * em_part_lds<MT, PPB, G>() + (size_t)b.mcap * kPrevBytes<G>;
     const dim3 grid((unsigned)groups), block(kPartThreads * parts);
     auto kernel = a.tables ? k_em_mfma<MT, kSrcPre, SPLIT, PPB, G, PARTS> : k_em_mfma<MT, kSrcGlobal, SPLIT, PPB, G, PARTS>;
@@ -1121,8 +1124,12 @@ static int launch_em_mfma(const EmMfmaArgs &a, hipStream_t st)
     return PM_OK;
 }
 
-// tile shape in use per (ceil(l/4) - 1, split), coded 10 G + PPB; 0 = untuned
+// tile shape in use per (ceil(l/4) - 1, split), coded 10 G + PPB; 0 = untuned.
+// With kShapeSet: set by the caller, and taken by every launch
 static int g_shape[8][2];
+constexpr int kShapeSet = 256;
+
+static int &shape_of(int l, bool split) { return g_shape[(l + 3) / 4 - 1][split ? 1 : 0]; }
 
 static bool shape_ok(int shape, int l)
 {
@@ -1132,7 +1139,7 @@ static bool shape_ok(int shape, int l)
 
 static int tuned_shape(int l, bool split)
 {
-    const int v = g_shape[(l + 3) / 4 - 1][split ? 1 : 0];
+    const int v = shape_of(l, split) & ~kShapeSet;
     return v ? v : kShapeDefault;
 }
 
@@ -1155,8 +1162,8 @@ static int dispatch_mt(const EmMfmaArgs &a, hipStream_t st)
 template <bool SPLIT>
 static int dispatch_shape(const EmMfmaArgs &a, hipStream_t st, int shape)
 {
-    if (em_parts(a) > 1) return dispatch_mt<SPLIT, kPartsPPB, 1, true>(a, st);
     switch (shape) {
+    case kShapeParts: return dispatch_mt<SPLIT, kPartsPPB, 1, true>(a, st);
     case 11: return dispatch_mt<SPLIT, 1, 1>(a, st);
     case 12: return dispatch_mt<SPLIT, 2, 1>(a, st);
     case 14: return dispatch_mt<SPLIT, 4, 1>(a, st);
@@ -1166,21 +1173,17 @@ static int dispatch_shape(const EmMfmaArgs &a, hipStream_t st, int shape)
     }
 }
 
-// the tile shape a launch runs in (0: the one recorded for the length class and
-// precision)
-static int launch_shape(const EmMfmaArgs &a, int shape)
+// the tile shape a launch runs in: in parts where those pay, unless the caller
+// has set a shape; else the recorded one
+static int launch_shape(const EmMfmaArgs &a)
 {
-    if (!shape) shape = tuned_shape(a.l, a.split != 0);
-    if (!shape_ok(shape, a.l)) shape = 10 + shape % 10;
-    // two groups of models per wave halve the workgroups; where there are too
-    // few already, and the workgroups come in parts, one group per wave
-    return em_parts(a) > 1 ? 10 + kPartsPPB : shape;
+    if (!(shape_of(a.l, a.split != 0) & kShapeSet) && em_parts(a) > 1) return kShapeParts;
+    const int shape = tuned_shape(a.l, a.split != 0);
+    return shape_ok(shape, a.l) ? shape : 10 + shape % 10;
 }
 
-// shape 0: the one recorded for this length class and precision
-static int dispatch_em_mfma(const EmMfmaArgs &a, hipStream_t st, int shape = 0)
+static int dispatch_em_mfma(const EmMfmaArgs &a, hipStream_t st, int shape)
 {
-    shape = launch_shape(a, shape);
     return a.split ? dispatch_shape<true>(a, st, shape) : dispatch_shape<false>(a, st, shape);
 }
 
@@ -1208,7 +1211,7 @@ int em_refine_mfma(const pm_seqs *S, int32_t l, const double *theta0, const doub
     a.beta = beta;
     const int rc = prepare_tables(a, S, l, ws, ws_bytes, st);
     if (rc != PM_OK) return rc;
-    return dispatch_em_mfma(a, st);
+    return dispatch_em_mfma(a, st, launch_shape(a));
 }
 
 // One workgroup: each instance's bucket range (buckets ascend by item), its
@@ -1314,9 +1317,9 @@ int em_refine_mfma_batch(const pm_batch *Bt, int64_t nw_max, int t_max, const pm
     a.l = Bt->l;
     a.iters = iters;
     a.beta = beta;
-    const int shape = launch_shape(a, 0);
+    const int shape = launch_shape(a);
     hipLaunchKernelGGL(k_em_plan, dim3(1), dim3(1024), 0, st, Bt->inst, Bt->P, buckets, n_dev, B,
-                       16 * kWaves * (shape / 10), plan, tbase);
+                       16 * kWaves * shape_groups(shape), plan, tbase);
     PM_LAUNCHED();
     EmTabArgs tt{};
     tt.inst = Bt->inst;
@@ -1376,7 +1379,7 @@ int em_autotune_mfma(const pm_seqs *S, int32_t l, const double *theta0, const do
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != PM_OK) return rc;
-    g_shape[(l + 3) / 4 - 1][split ? 1 : 0] = best;
+    shape_of(l, split) = best;
     if (choice) *choice = best;
     return PM_OK;
 }
@@ -1388,7 +1391,7 @@ int em_record_shape(int32_t l, bool split, int32_t shape)
     if (!shape_ok(shape, l))
         return fail(PM_EINVAL, "tile shape %d is not one of 11, 12, 14, 21, 22, 24 (G = 2 needs l <= %d)", shape,
                     4 * kMaxMT2);
-    g_shape[(l + 3) / 4 - 1][split ? 1 : 0] = shape;
+    shape_of(l, split) = shape | kShapeSet;
     return PM_OK;
 }
 

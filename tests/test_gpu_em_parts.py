@@ -48,7 +48,7 @@ LENS = {"1": [150], "2": [90, 400], "3": [64, 65, 300], "4": [40, 200, 33, 500],
 
 
 @pytest.mark.parametrize("prec", [pm.PM_F16X2, pm.PM_F16], ids=["f16x2", "f16"])
-@pytest.mark.parametrize("l,lens", [(12, "1"), (12, "2"), (18, "3"), (18, "4"), (18, "20"), (22, "20"), (27, "20"),
+@pytest.mark.parametrize("l,lens", [(14, "1"), (14, "2"), (18, "3"), (18, "4"), (18, "20"), (22, "20"), (27, "20"),
                                     (31, "4"), (15, "61"), (3, "20")])
 def test_same_bits_with_any_room(l, lens, prec):
     rng = np.random.default_rng([l, len(lens)])
