@@ -28,8 +28,9 @@ struct SelWs {
     int64_t *bb;      // [m] first bucket of the trial
     int64_t *mb;      // [m] first member slot of the trial
     int64_t *n_heavy; // [1] trials with more buckets than the first emit launch takes
-    int64_t *qctr;    // [4] next unit of the heavy launch (its work queue's head, [0])
-    int32_t *heavy;   // [m] those trials, in order
+    int64_t *qctr;    // [4] next units of the heavy launches (their work queues' heads, [0] and [1]), and
+                      // whether the second has anything to do ([2])
+    int32_t *heavy;   // [m] those trials, in order; kHasBig set: buckets are left to the second launch
     int64_t *nep;     // [m][parts] buckets of each part of a trial's bins (parts > 1)
     int64_t *msp;     // [m][parts] their members
     uint64_t *bits;   // [m][nwb] passing keys: bit key % 64 of word key / 64
@@ -92,7 +93,8 @@ struct SelArgs {
     int nwb;    // bitmap words, ceil(nb / 64)
     int cb;     // buckets whose cursors the LDS holds
     int parts;  // k_sel_count: workgroups per trial
-    int room;   // k_sel_emit_heavy: bytes of LDS for rows and list
+    int room;   // k_sel_emit_heavy, k_sel_emit_cursors: bytes of LDS for rows and list or cursors
+    int cursors;  // k_sel_emit_cursors follows k_sel_emit_heavy
 };
 
 // per (trial, part of its bins): number of passing bins, their total size
@@ -649,7 +651,7 @@ __global__ void __launch_bounds__(256) k_sel_emit(const SelArgs a)
     extern __shared__ __align__(16) uint64_t bm[];
     __shared__ uint32_t tmp[256];
     const int j = blockIdx.x;
-    if (j == 0 && threadIdx.x == 0) a.ws.qctr[0] = 0;  // the heavy launch's queue, for after this one
+    if (j == 0 && threadIdx.x < 3) a.ws.qctr[threadIdx.x] = 0;  // of the heavy launches after this one
     const int64_t ne = a.ws.ne[j];
     if (ne == 0 || ne > a.cb || heavy_members(ne, a.ws.ms[j], a.light)) return;
     emit_trial(a, j, ne, bm, tmp);
@@ -663,7 +665,8 @@ __global__ void __launch_bounds__(256) k_sel_emit(const SelArgs a)
 // its bucket's piece of it, which is its rank.  A bucket holds few members (s
 // and somewhat more), so that is a handful of LDS reads, and slots are written
 // side by side.  A bucket of more than kHeavyBig members is left out of the
-// list; a wave goes through the windows for it.
+// list: k_sel_emit_cursors places it, or in small instances a wave that goes
+// through the windows for it.
 //
 // Keys, counts and first slots go by a thread per bucket, so that a trial
 // waits for its counts once, not once for every few bitmap words.  A trial
@@ -681,6 +684,14 @@ constexpr int kHeavyU = 8;               // key loads in flight per lane
 constexpr uint32_t kHeavyBig = 128;
 constexpr int kHeavyBigs = 256;          // big buckets of a range: the list's places / kHeavyBig at most
 constexpr uint32_t kNotListed = 0x80000000u;
+constexpr int32_t kHasBig = INT32_MIN;
+// k_sel_emit_cursors is launched for instances of more windows: below, no trial
+// of more than kSelChunk / 2 buckets is dense, and big buckets are few
+constexpr int64_t kCursorWindows = 32 * kSelChunk / 2;
+
+// trials placed by k_sel_emit_cursors alone: ranking takes a bucket's members
+// times themselves (see heavy_members)
+__device__ __forceinline__ bool heavy_dense(int64_t buckets, int64_t members) { return members > 32 * buckets; }
 constexpr uint16_t kNoBucket = 0xffffu;
 
 // exclusive prefix sums of n values in place, v[n] receiving the total
@@ -721,8 +732,10 @@ __device__ __forceinline__ int heavy_reach(const uint32_t *v, int lo, int n, uin
 }
 
 // trial j (ne passing keys); of several workgroups that share it, number `part`
-// of `parts` takes every parts-th range
-__device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, int part, int parts, uint64_t *bm)
+// of `parts` takes every parts-th range; *seen (LDS): non-zero if there were big
+// buckets
+__device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, int part, int parts, uint64_t *bm,
+                                           uint32_t *seen)
 {
     __shared__ uint32_t scan[kHeavyWaves];
     __shared__ uint32_t big_key[kHeavyBigs], big_first[kHeavyBigs], n_big;
@@ -856,7 +869,7 @@ __device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, 
                 if (slot < a.cap_m) a.members[slot] = w;
             }
             // ---- big buckets: a wave finds a key's windows in order
-            const uint32_t nb = min(n_big, (uint32_t)kHeavyBigs);
+            const uint32_t nb = a.cursors ? 0u : min(n_big, (uint32_t)kHeavyBigs);
             for (uint32_t q = wv; q < nb; q += kHeavyWaves) {
                 const uint32_t key = big_key[q];
                 int64_t slot = mbase + m_rows + big_first[q];
@@ -877,7 +890,10 @@ __device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, 
                 }
             }
             __syncthreads();
-            if (tid == 0) n_big = 0;
+            if (tid == 0) {
+                *seen |= n_big;
+                n_big = 0;
+            }
             __syncthreads();
         }
         m_rows += first[n];
@@ -895,6 +911,7 @@ __global__ void __launch_bounds__(kHeavyThreads, 8) k_sel_emit_heavy(const SelAr
 {
     extern __shared__ __align__(16) uint64_t bm[];
     __shared__ int64_t claim;
+    __shared__ uint32_t seen;
     const int64_t nh = *a.ws.n_heavy;
     if (nh == 0) return;  // no queue traffic
     const int parts = (int)(nh >= gridDim.x ? 1 : min((int64_t)8, ((int64_t)gridDim.x + nh - 1) / nh));
@@ -905,11 +922,216 @@ __global__ void __launch_bounds__(kHeavyThreads, 8) k_sel_emit_heavy(const SelAr
         const int64_t un = claim;
         __syncthreads();
         if (un >= nh * parts) break;  // every workgroup ends here once the queue is past its end
-        const int j = a.ws.heavy[un % nh], part = (int)(un / nh);
+        const int j = a.ws.heavy[un % nh] & ~kHasBig, part = (int)(un / nh);
         const int64_t ne = a.ws.ne[j];
+        const int64_t ms = a.ws.ms[j];
+        if (threadIdx.x == 0) seen = a.cursors && heavy_dense(ne, ms);
         // a trial that fits the LDS is one range
-        if (part > 0 && 8 * ne + 7 * a.ws.ms[j] + 1024 <= a.room) continue;  // uniform over the workgroup
-        emit_heavy(a, j, ne, part, parts, bm);
+        if (!(a.cursors && heavy_dense(ne, ms)) && (part == 0 || 8 * ne + 7 * ms + 1024 > a.room))  // uniform
+            emit_heavy(a, j, ne, part, parts, bm, &seen);
+        if (a.cursors && threadIdx.x == 0 && seen) {
+            atomicOr(a.ws.heavy + claim % *a.ws.n_heavy, kHasBig);
+            a.ws.qctr[2] = 1;
+        }
+    }
+}
+
+// Buckets of many members, by cursors: a stable placement in two passes over
+// the windows, of which each of the sixteen waves takes a sixteenth (it counts
+// the buckets' members; the counts of the waves give each its first slots; it
+// places its members in order).  All buckets of a dense trial, with their
+// records, and the big ones of the others.  A trial goes by ranges of as many
+// buckets as the LDS has cursors for.  Bound by LDS accesses: a key's bucket is
+// one read of a table where the range's keys are few enough (three dependent
+// reads by the bitmap), and lanes that meet on a bucket show by the value that
+// the cursor has after the step, so that only those are put in order by ballots.
+// Whole selection of 256 DNA trials of 200 000 windows (k = 6, 49 members per
+// bucket) 1410 us so, 1670 by ranks, 1180 by four waves' cursors; of 1024 such
+// trials 4700, 5930 and 4560 (all members' slots lie apart: bound by their
+// writes); of 64 trials of 520 000 (127 per bucket) 1050, 26 000 and 2110.  At
+// 24 per bucket (1024 trials of 100 000) ranks take 2010, four waves' cursors
+// 2710; the line between the two lies at 32 (heavy_dense).
+constexpr int kCursorU = 8;  // windows per lane and step
+constexpr int kMapKeys = 10240;
+
+__device__ __forceinline__ int cursor_rows(int room) { return (room - 4 - 2 * kMapKeys) / (8 + 4 * kHeavyWaves); }
+
+__device__ __forceinline__ void emit_cursors(const SelArgs &a, int j, int64_t ne, bool dense, int part, int parts,
+                                             uint64_t *bm)
+{
+    __shared__ uint32_t scan[kHeavyWaves];
+    __shared__ uint32_t n_big;
+    uint32_t *wcnt = reinterpret_cast<uint32_t *>(bm + a.nwb);  // [nwb + 1] -> buckets before the word
+    uint32_t *num = wcnt + a.nwb + 1;                           // [rcap] key, then number of the row's bucket
+    const int rcap = cursor_rows(a.room);
+    uint32_t *first = num + rcap;                               // [rcap + 1] first slot within the rows' buckets
+    uint32_t *cursors = first + rcap + 1;                       // [kHeavyWaves][numbers] next slots
+    uint16_t *map = reinterpret_cast<uint16_t *>(cursors + kHeavyWaves * rcap);  // [kMapKeys] numbers by key
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
+    const uint32_t *cnt = a.counts + (int64_t)j * a.nb;
+    const uint64_t *bits = a.ws.bits + (int64_t)j * a.nwb;
+    const int64_t bbase = a.ws.bb[j], mbase = a.ws.mb[j];
+    const pm_inst I = a.inst ? a.inst[a.item_inst[j]] : a.one;
+    const uint32_t *kj = a.keys + I.key_base + (int64_t)(j - I.first_item) * I.x;
+    const uint32_t x = (uint32_t)I.x;  // below 2^31
+    const uint32_t lo = (uint32_t)((uint64_t)x * wv / kHeavyWaves), hi = (uint32_t)((uint64_t)x * (wv + 1) / kHeavyWaves);
+
+    for (int w = tid; w < a.nwb; w += kHeavyThreads) {
+        const uint64_t b = word_in_key_order(bits[w]);
+        bm[w] = b;
+        wcnt[w] = (uint32_t)__popcll(b);
+    }
+    __syncthreads();
+    heavy_scan(wcnt, a.nwb, scan);
+
+    int64_t slot0 = mbase;  // first slot of the rows' buckets
+    for (int w0 = 0, w1, r = 0; w0 < a.nwb; w0 = w1) {
+        // ---- the buckets of as many words as there are rows for
+        w1 = heavy_reach(wcnt, w0, a.nwb, (uint32_t)rcap);
+        const uint32_t b0 = wcnt[w0], wn = (uint32_t)(w1 - w0);
+        const int n = (int)(wcnt[w1] - b0);  // at most rcap: a word has 64
+        if (n == 0) continue;
+        for (uint32_t u = tid; u < 4 * wn; u += kHeavyThreads) {
+            const int w = w0 + (int)(u >> 2), sh = 16 * (u & 3);
+            const uint64_t b = bm[w];
+            uint32_t at = wcnt[w] - b0 + (uint32_t)__popcll(b & ((1ull << sh) - 1ull));
+            for (uint32_t q = (uint32_t)(b >> sh) & 0xffffu; q; q &= q - 1u)
+                num[at++] = (uint32_t)w * 64u + (uint32_t)(sh + __ffs((int)q) - 1);
+        }
+        if (tid == 0) n_big = 0;
+        const uint32_t k0 = 64u * (uint32_t)w0, kn = 64u * wn;  // the range's keys
+        const bool mapped = kn <= (uint32_t)kMapKeys;
+        if (mapped)
+            for (uint32_t d = tid; d < kn; d += kHeavyThreads) map[d] = 0xffffu;
+        __syncthreads();
+        for (int i = tid; i < n; i += kHeavyThreads) first[i] = cnt[num[i]];
+        __syncthreads();
+        heavy_scan(first, n, scan);
+        for (int i = tid; i < n; i += kHeavyThreads) {
+            const int64_t b = bbase + b0 + i;
+            const uint32_t f = first[i], c = first[i + 1] - f;
+            const bool kept = b < a.cap_b;
+            if (kept && dense && part == 0) a.buckets[b] = pm_bucket{(uint32_t)j, num[i], c, (uint32_t)(slot0 + f)};
+            const uint32_t q = kept && (dense || c > kHeavyBig) ? atomicAdd(&n_big, 1u) : 0xffffffffu;
+            if (mapped) map[num[i] - k0] = (uint16_t)q;
+            num[i] = q;
+        }
+        __syncthreads();
+        const uint32_t nq = n_big;
+        // a trial's ranges are shared by `parts` workgroups; a range without big
+        // buckets needs none
+        if (nq > 0 && r++ % parts == part) {
+            uint32_t *mine = cursors + wv * nq;
+            // the number of a key's bucket (nq or more: none)
+            auto number = [&](uint32_t key) {
+                // (0xffffffff, where there is no window or key, is in no range)
+                if (mapped) return key - k0 < kn ? (uint32_t)map[key - k0] : 0xffffffffu;
+                const uint32_t wd = key >> 6;
+                if (wd - (uint32_t)w0 >= wn) return 0xffffffffu;
+                const uint64_t m = bm[wd];
+                if (!((m >> (key & 63u)) & 1ull)) return 0xffffffffu;
+                return num[wcnt[wd] + (uint32_t)__popcll(m & ((1ull << (key & 63u)) - 1ull)) - b0];
+            };
+            uint32_t nk[kCursorU];  // the next step's keys, loaded ahead
+            auto load_keys = [&](uint32_t wb) {
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) {
+                    const uint32_t w = wb + 64 * u + lane;
+                    nk[u] = w < hi ? kj[w] : 0xffffffffu;
+                }
+            };
+            for (uint32_t e = tid; e < kHeavyWaves * nq; e += kHeavyThreads) cursors[e] = 0;
+            load_keys(lo);
+            __syncthreads();
+            for (uint32_t wb = lo; wb < hi; wb += 64 * kCursorU) {
+                uint32_t q[kCursorU];
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) q[u] = nk[u];
+                load_keys(wb + 64 * kCursorU);
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) q[u] = number(q[u]);
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u)
+                    if (q[u] < nq) atomicAdd(mine + q[u], 1u);
+            }
+            load_keys(lo);
+            __syncthreads();
+            for (int i = tid; i < n; i += kHeavyThreads) {
+                const uint32_t q = num[i];
+                if (q >= nq) continue;
+                uint32_t run = first[i], c[kHeavyWaves];
+#pragma unroll
+                for (int w = 0; w < kHeavyWaves; ++w) c[w] = cursors[w * nq + q];
+#pragma unroll
+                for (int w = 0; w < kHeavyWaves; ++w) {
+                    cursors[w * nq + q] = run;
+                    run += c[w];
+                }
+            }
+            __syncthreads();
+            for (uint32_t wb = lo; wb < hi; wb += 64 * kCursorU) {
+                uint32_t q[kCursorU], old[kCursorU], now[kCursorU];
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) q[u] = nk[u];
+                load_keys(wb + 64 * kCursorU);
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) q[u] = number(q[u]);
+                // the steps in order: a wave's LDS operations complete in order
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) {
+                    old[u] = 0;
+                    now[u] = 1;
+                    if (q[u] < nq) {
+                        old[u] = __hip_atomic_fetch_add(mine + q[u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        now[u] = __hip_atomic_load(mine + q[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kCursorU; ++u) {
+                    uint64_t met = __ballot(now[u] != old[u] + 1u);
+                    while (met) {
+                        // lanes of one bucket, all but one of which see a larger
+                        // value: their slots in lane order
+                        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane(
+                            (int)q[u], __ffsll((unsigned long long)met) - 1);
+                        const uint64_t peers = __ballot(q[u] == b);
+                        if (q[u] == b)
+                            old[u] = now[u] - (uint32_t)__popcll(peers) + (uint32_t)__popcll(peers & lanemask_lt());
+                        met &= ~peers;
+                    }
+                    const int64_t slot = slot0 + old[u];
+                    if (q[u] < nq && slot < a.cap_m) a.members[slot] = wb + 64 * u + lane;
+                }
+            }
+        }
+        __syncthreads();
+        slot0 += first[n];
+        __syncthreads();
+    }
+}
+
+__global__ void __launch_bounds__(kHeavyThreads, 4) k_sel_emit_cursors(const SelArgs a)
+{
+    extern __shared__ __align__(16) uint64_t bm[];
+    __shared__ int64_t claim;
+    if (a.ws.qctr[2] == 0) return;
+    const int64_t nh = *a.ws.n_heavy;
+    const int parts = (int)(nh >= gridDim.x ? 1 : min((int64_t)8, ((int64_t)gridDim.x + nh - 1) / nh));
+    unsigned long long *q = reinterpret_cast<unsigned long long *>(a.ws.qctr + 1);
+    for (;;) {
+        if (threadIdx.x == 0) claim = (int64_t)atomicAdd(q, 1ull);
+        __syncthreads();
+        const int64_t un = claim;
+        __syncthreads();
+        if (un >= nh * parts) break;  // every workgroup ends here once the queue is past its end
+        const int32_t entry = a.ws.heavy[un % nh];
+        const int j = entry & ~kHasBig, part = (int)(un / nh);
+        const int64_t ne = a.ws.ne[j];
+        const bool dense = heavy_dense(ne, a.ws.ms[j]);
+        if (!dense && entry >= 0) continue;  // uniform over the workgroup
+        // a trial that fits the LDS is one range
+        if (part > 0 && ne <= cursor_rows(a.room)) continue;
+        emit_cursors(a, j, ne, dense, part, parts, bm);
     }
 }
 
@@ -1072,6 +1294,8 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
         (void)hipFuncSetAttribute((const void *)k_sel_emit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
         (void)hipFuncSetAttribute((const void *)k_sel_emit_heavy, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds_max);
+        (void)hipFuncSetAttribute((const void *)k_sel_emit_cursors, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds_max);
         (void)hipGetLastError();  // an unsupported attribute must not poison the launch check
         attr = true;
     }
@@ -1085,8 +1309,16 @@ static int select_launch(SelArgs &a, int64_t x_max, hipStream_t st, bool counted
         const int64_t lds = half - 12 * nwb >= half / 3 ? half : lds_max & ~(int64_t)7;
         a.room = (int)(lds - 12 * nwb - 8);
         const int grid = (int)std::min<int64_t>(8 * (int64_t)a.m, lds == half ? 512 : 256);
+        a.cursors = x_max > kCursorWindows;
         hipLaunchKernelGGL(k_sel_emit_heavy, dim3(grid), dim3(kHeavyThreads), (size_t)lds, st, a);
         PM_LAUNCHED();
+        if (a.cursors) {
+            const int64_t all = lds_max & ~(int64_t)7;
+            a.room = (int)(all - 12 * nwb - 8);
+            const int grid1 = (int)std::min<int64_t>(8 * (int64_t)a.m, 256);
+            hipLaunchKernelGGL(k_sel_emit_cursors, dim3(grid1), dim3(kHeavyThreads), (size_t)all, st, a);
+            PM_LAUNCHED();
+        }
     }
     return PM_OK;
 }
