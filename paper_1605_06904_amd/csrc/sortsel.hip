@@ -19,7 +19,9 @@
 // is one slice, and the sort is of what passes it, commonly some dozens of
 // pairs.  1000 trials of the (18,6) workload, k = 14, s = 2: 2740 us without it,
 // 362 with one look, 238 with a second one over what passed; bound by the keys,
-// formed once per pass, and the LDS atomics of the first look.
+// formed once per pass, and the LDS atomics of the first look.  Kernels of their
+// own for the two forms: without the filter's code the other one takes 3 to 10%
+// less.
 // Nothing but the bucket records and members reaches HBM; like the fused
 // count-table path, one pass counts (per-slice totals, scanned on the device)
 // and a second identical pass writes.
@@ -34,6 +36,15 @@ constexpr int kFiltCap = 4096;     // the same behind the filter
 constexpr int kFiltLog = 18;       // log2 bits of the filter's first bitmap (it lies in the buffer)
 static_assert(kFiltCap * 64 == 1 << kFiltLog, "the bitmap lies in the sort buffer");
 constexpr int kFiltWindows = 24;   // filtered windows per thread whose keys stay in registers
+// The filter needs keys that are rarely met twice: at least this many keys per
+// window, from where on what passes still fits the buffer.  Random DNA, k = 8,
+// s = 2, unfiltered against filtered: 300 trials of 20 000 windows (3.3 keys per
+// window) 970 and 576 us, 150 of 30 000 (2.2) 750 and 734, of 40 000 (1.6) 1213
+// and 1280, of 80 000 (0.8) 3040 and 4100.  A trial is not one slice where
+// there are fewer trials than CUs: 12 trials of 80 000 windows, k = 9, 788 us in
+// four slices, 271 in 20.
+constexpr int64_t kFiltSparse = 2;
+constexpr int64_t kSortCUs = 256;
 constexpr int kCoarseLog = 12;
 constexpr int kCoarseBins = 1 << kCoarseLog;  // key ranges of the coarse histogram
 constexpr int kCtlWords = 64;      // block-scan partials and round state
@@ -42,8 +53,6 @@ constexpr int kSortWaves = kHashThreads / kWave;
 struct HsortArgs {
     HashArgs h;
     uint32_t s;
-    int cap;                        // pairs of the sort buffer
-    int filt;                       // log2 bits of the filter's first bitmap (in the sort buffer), 0: no filter
     uint64_t slice_width;           // keys per slice (the last one may be shorter)
     int64_t *tot_b, *tot_m;         // [items * nslices]
     const int64_t *base_b, *base_m; // [items * nslices] (EMIT)
@@ -95,7 +104,7 @@ __device__ __forceinline__ int coarse_shift(uint64_t range)
     return sh;
 }
 
-template <int A, int K, bool EMIT>
+template <int A, int K, bool EMIT, bool FILT>
 __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
 {
     const HashArgs &a = g.h;
@@ -114,12 +123,12 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
         }
         return;
     }
-    const uint32_t cap = (uint32_t)g.cap;
+    constexpr uint32_t cap = FILT ? kFiltCap : kSortCap;
     uint64_t *buf = reinterpret_cast<uint64_t *>(smem);  // [cap]
     uint32_t *hist = smem + 2 * cap;                      // [kCoarseBins]
     uint32_t *ctl = hist + kCoarseBins;                   // [kCtlWords]
     uint32_t *twice = ctl + kCtlWords;                    // filter's second bitmap
-    uint32_t *seq = twice + (g.filt ? filt_words2(g.filt) : 0);
+    uint32_t *seq = twice + (FILT ? filt_words2(kFiltLog) : 0);
     int32_t *wst = reinterpret_cast<int32_t *>(seq + a.seq_cap);
     const Staged st = stage_input<A>(a, j, seq, wst);
     int pos[K];
@@ -140,18 +149,18 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
     // coincidence, in about one window of ten).  Commonly they all fit the sort
     // buffer, and the slice is done after one look at its windows and one at
     // the keys kept from it.
-    auto hashed = [&](uint64_t key) { return ((uint32_t)key * 0x9E3779B1u) >> (32 - g.filt); };
+    auto hashed = [&](uint64_t key) { return ((uint32_t)key * 0x9E3779B1u) >> (32 - kFiltLog); };
     auto marked = [&](uint64_t key) {
-        if (!g.filt) return true;
+        if (!FILT) return true;
         const uint32_t h = hashed(key) >> kFiltFold;
         return ((twice[h >> 5] >> (h & 31u)) & 1u) != 0;
     };
     bool whole = false;  // the slice's pairs are in buf
     uint32_t n_whole = 0;
-    if (g.filt) {
+    if constexpr (FILT) {
         uint32_t *once = smem;  // the sort buffer's words
-        for (int b = tid; b < (1 << g.filt) / 32; b += kHashThreads) once[b] = 0;
-        for (int b = tid; b < filt_words2(g.filt); b += kHashThreads) twice[b] = 0;
+        for (int b = tid; b < (1 << kFiltLog) / 32; b += kHashThreads) once[b] = 0;
+        for (int b = tid; b < filt_words2(kFiltLog); b += kHashThreads) twice[b] = 0;
         if (tid == 0) ctl[2 * kSortWaves + 2] = 0;
         __syncthreads();
         const bool all_keys = s_lo == 0 && s_hi >= (uint64_t)a.nb;
@@ -209,7 +218,7 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
             uint64_t mine[kPer];
             auto hashed2 = [](uint64_t pair) { return ((uint32_t)(pair >> 32) * 0xB5297A4Du) >> (32 - kCoarseLog - 5); };
             for (int b = tid; b < kCoarseBins; b += kHashThreads) hist[b] = 0;
-            for (int b = tid; b < filt_words2(g.filt); b += kHashThreads) twice[b] = 0;
+            for (int b = tid; b < filt_words2(kFiltLog); b += kHashThreads) twice[b] = 0;
             if (tid == 0) ctl[2 * kSortWaves + 2] = 0;
             __syncthreads();
 #pragma unroll
@@ -409,36 +418,38 @@ __global__ void __launch_bounds__(kHashThreads) k_hsort(const HsortArgs g)
     }
 }
 
-template <int A, int K, bool EMIT>
+template <int A, int K, bool EMIT, bool FILT>
 static int launch_hsort(const HsortArgs &g, size_t lds, int blocks, hipStream_t st)
 {
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_hsort<A, K, EMIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void *)k_hsort<A, K, EMIT, FILT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   device_lds_bytes());
         (void)hipGetLastError();
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_hsort<A, K, EMIT>), dim3(blocks), dim3(kHashThreads), lds, st, g);
+    hipLaunchKernelGGL((k_hsort<A, K, EMIT, FILT>), dim3(blocks), dim3(kHashThreads), lds, st, g);
     PM_LAUNCHED();
     return PM_OK;
 }
 
 // run-time (alphabet, k) -> compile-time kernel: DNA k 8..16, protein k 4..7
-template <int K>
+template <bool FILT, int K>
 static int dispatch_hsort(int alphabet, int k, bool emit, const HsortArgs &g, size_t lds, int blocks, hipStream_t st)
 {
     if constexpr (K > 16) {
         return fail(PM_ERANGE, "k=%d not supported by the sorted selection", k);
     } else {
-        if (k != K) return dispatch_hsort<K + 1>(alphabet, k, emit, g, lds, blocks, st);
+        if (k != K) return dispatch_hsort<FILT, K + 1>(alphabet, k, emit, g, lds, blocks, st);
         if (alphabet == 4) {
             if constexpr (K >= kSortKMinDna)
-                return emit ? launch_hsort<4, K, true>(g, lds, blocks, st) : launch_hsort<4, K, false>(g, lds, blocks, st);
+                return emit ? launch_hsort<4, K, true, FILT>(g, lds, blocks, st)
+                            : launch_hsort<4, K, false, FILT>(g, lds, blocks, st);
             return fail(PM_ERANGE, "k=%d below the sorted selection's range for DNA", k);
         }
         if constexpr (K >= kSortKMinProt && K <= 7)
-            return emit ? launch_hsort<20, K, true>(g, lds, blocks, st) : launch_hsort<20, K, false>(g, lds, blocks, st);
+            return emit ? launch_hsort<20, K, true, FILT>(g, lds, blocks, st)
+                        : launch_hsort<20, K, false, FILT>(g, lds, blocks, st);
         return fail(PM_ERANGE, "k=%d outside the sorted selection's range for protein", k);
     }
 }
@@ -507,15 +518,15 @@ int hsort_run(HashArgs &a, int A, int32_t items, int64_t x_max, int64_t nw_max, 
         return fail(PM_EINVAL, "workspace of %zu bytes, need %zu", ws_bytes, hsort_ws_bytes(entries));
     if (((uintptr_t)ws & 7) != 0) return fail(PM_EINVAL, "workspace must be 8-byte aligned");
     HsortArgs g{};
-    g.cap = kSortCap;
-    if (s >= 2) {
-        // filtered: as many windows per slice as a bitmap of the (halved)
-        // buffer's bits takes at one key in ten bits; never more slices
-        g.cap = kFiltCap;
-        g.filt = kFiltLog;
-        lds -= (size_t)(2 * (kSortCap - kFiltCap) - filt_words2(g.filt)) * 4;
+    const bool filtered = s >= 2 && kFiltSparse * x_max <= a.nb;
+    if (filtered) {
+        // as many windows per slice as a bitmap of the (halved)
+        // buffer's bits takes at one key in ten bits, but as many slices as
+        // there are CUs for; never more slices
+        lds -= (size_t)(2 * (kSortCap - kFiltCap) - filt_words2(kFiltLog)) * 4;
         const int64_t per = (int64_t)kFiltWindows * kHashThreads;
-        a.nslices = (int)std::max<int64_t>(1, std::min<int64_t>(a.nslices, (x_max + per - 1) / per));
+        a.nslices = (int)std::max<int64_t>(
+            1, std::min<int64_t>(a.nslices, std::max<int64_t>((x_max + per - 1) / per, kSortCUs / std::max(items, 1))));
         entries = (int64_t)items * a.nslices;
     }
     int64_t *w = static_cast<int64_t *>(ws);
@@ -530,11 +541,15 @@ int hsort_run(HashArgs &a, int A, int32_t items, int64_t x_max, int64_t nw_max, 
     g.members = members;
     g.cap_b = cap_b;
     g.cap_m = cap_m;
-    if (int rc = dispatch_hsort<1>(A, a.k, false, g, lds, (int)entries, st)) return rc;
+    const auto launch = [&](bool emit) {
+        return filtered ? dispatch_hsort<true, 1>(A, a.k, emit, g, lds, (int)entries, st)
+                        : dispatch_hsort<false, 1>(A, a.k, emit, g, lds, (int)entries, st);
+    };
+    if (int rc = launch(false)) return rc;
     const TotScan ts{g.tot_b, g.tot_m, w + 2 * entries, w + 3 * entries, entries, cap_b, cap_m, n_out, a.status};
     if (int rc = launch_tot_scan(ts, st)) return rc;
     if (cap_b == 0 && cap_m == 0) return PM_OK;  // sizing only
-    return dispatch_hsort<1>(A, a.k, true, g, lds, (int)entries, st);
+    return launch(true);
 }
 
 }  // namespace pm
