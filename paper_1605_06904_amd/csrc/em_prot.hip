@@ -39,7 +39,7 @@
 // 16 384 models of the (20,6) workload (t = 30, n = 1000), 5 iterations:
 // 32.1 ms with dense operands of both steps rebuilt in LDS for every window
 // pair and read by every wave for its own 16 models; 8.1 ms with every wave
-// doing both steps (a wave per SIMD with all registers, or two), 6.2 ms so: an
+// doing both steps (a wave per SIMD with all registers, or two), 6.3 ms so: an
 // E-step wave is the longest in every step (about 2 100 cycles per block, of
 // which 450 are its matrix instructions).
 //
@@ -418,13 +418,13 @@ __device__ __forceinline__ void prot_wave(const EmProtArgs &a, uint8_t *dyn, Pro
                     }
 #pragma unroll
                     for (int q = 0; q < kPE; ++q) {
-                        float e[8];
+                        double e[8];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
-                            e[j] = __builtin_amdgcn_exp2f(S[0][q][j]);
-                            e[4 + j] = __builtin_amdgcn_exp2f(S[1][q][j]);
+                            e[j] = (double)__builtin_amdgcn_exp2f(S[0][q][j]);
+                            e[4 + j] = (double)__builtin_amdgcn_exp2f(S[1][q][j]);
                         }
-                        sm[q] += (double)(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
+                        sm[q] += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
                     }
                 }
                 // the four lanes of each model (a lane without a window has the
