@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
     for (int i = 0; i < t; ++i) {
         const int64_t s0 = O[i], L = O[i + 1] - s0 - l + 1;
         double bv = -INFINITY;
-        int64_t ba = INT64_MAX;
+        int64_t ba = lane < L ? lane : INT64_MAX;  // (no finite score: the first start)
         for (int64_t a = lane; a < L; a += kWave) {
             const double v = start_score(W, s0, a, Tw, l);
             if (v > bv) {
@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
         for (int a = lane; a < L; a += kWave) mx = fmax(mx, weight3<NG, false>(load_win(W, s0 + a), T3));
         mx = wave_max(mx);
         double bv = -INFINITY;
-        int64_t ba = INT64_MAX;
+        int64_t ba = lane < L ? lane : INT64_MAX;  // (no finite score: the first start)
         for (int a = lane; a < L; a += kWave) {
             const Win w = load_win(W, s0 + a);
             if (weight3<NG, false>(w, T3) >= mx - tol) {
