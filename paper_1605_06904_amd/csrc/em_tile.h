@@ -372,8 +372,9 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) k_em_tile(const EmArgs a)
                 if (__ballot(by_log)) {
                     const double lsite = lmix - log((double)L) + rf + log(sum);
                     if (by_log) qi = exp(lsite - log_add(lnone, lsite));
+                    if (!(sum > 0)) sum = 1.0;  // no finite score: qi = 0 and no counts
                 }
-                f = sum > 0 ? qi / sum : qi;  // (no finite score: no counts)
+                f = qi / sum;
             }
             if (last) {
                 if (a.sites) {
