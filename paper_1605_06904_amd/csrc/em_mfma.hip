@@ -160,15 +160,18 @@ constexpr int kMaxMT2 = 6;         // G = 2 for ceil(l/4) <= 6 (registers)
 constexpr float kPOff = 3.0f;
 constexpr float kSlack = 12.0f;
 // A known sequence's reference starts this far below its largest score of the
-// iteration before: room for it to fall by kBelow + kPOff bits (else the
+// iteration before (rounded up): room for it to fall by kBelow bits (else the
 // iteration is repeated) and to rise by kSlack - kBelow (else the reference
 // moves).  On the (12,4) to (24,7) shapes the largest score of a sequence
 // changes by -8 to +8 bits from theta0 to theta1 (medians near +2, 1% beyond
 // -6 and +5) and by less than 6 bits either way afterwards.
 constexpr float kBelowFirst = 8.0f;  // iteration 1
-constexpr float kBelow = 4.0f;       // later ones
-constexpr float kTopMin = 0.0f;  // smallest largest shifted score of such a sweep: a term of 1, whose
-                                 // FP16 halves still hold 24 bits down to 2^-24
+constexpr float kBelow = 5.0f;       // later ones
+// smallest largest shifted score of such a sweep: what a reference that moves
+// leaves at least (kPOff - 1), so that the FP16 halves of the small terms keep
+// as many bits
+constexpr float kTopMin = kPOff - 1.0f;
+static_assert(kTopMin == 2.0f, "terms of 2^2 and more");
 
 // 32 DNA symbols starting at P (MSB-first) as hi (P..P+15) and lo (P+16..P+31).
 // CLAMP: reads clamped below nw (global memory); otherwise the buffer is padded.
