@@ -79,6 +79,17 @@ __device__ __forceinline__ double gibbs_uniform(uint64_t seed, int sweep, int i,
     return (double)(c[0] >> 11) * (1.0 / 9007199254740992.0);
 }
 
+// LDS written by lanes of the wave before, read by other lanes after: the
+// hardware takes a wave's LDS operations in order, and the fences (no
+// instructions at this scope) keep the compiler from holding a value that
+// another lane has changed
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // score of start a of the sequence beginning at symbol s0 under table Wt
 __device__ __forceinline__ double start_score(const uint32_t *W, int64_t s0, int64_t a, const double *Wt, int l)
 {
@@ -150,7 +161,7 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
 
     // start: the best start of every sequence under theta0 (first on ties)
     for (int e = lane; e < AL; e += kWave) Tw[e] = log(g.theta0[b * AL + e]) - log(bgs[e / l]);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int i = 0; i < t; ++i) {
         const int64_t s0 = O[i], L = O[i + 1] - s0 - l + 1;
         double bv = -INFINITY;
@@ -166,10 +177,10 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
         if (lane == 0) cs[i] = (int32_t)ba;
     }
     for (int e = lane; e < AL; e += kWave) n[e] = 0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int i = 0; i < t; ++i)
         if (lane < l) atomicAdd(&n[(int)prot_sym(W, O[i] + cs[i] + lane) * l + lane], 1);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     double Fb = alignment_F(n, bgs, A, l, t, beta);
     const int it1 = g.sweeps + 1;
     if (g.F && lane == 0) g.F[b * it1] = Fb;
@@ -180,14 +191,14 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
         for (int i = 0; i < t; ++i) {
             const int64_t s0 = O[i], L = O[i + 1] - s0 - l + 1;
             // the other t-1 sites' model
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             if (lane < l) atomicSub(&n[(int)prot_sym(W, s0 + cs[i] + lane) * l + lane], 1);
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             for (int e = lane; e < AL; e += kWave) {
                 const int c = e / l;
                 Tw[e] = log(((double)n[e] + beta * bgs[c]) / tm1) - log(bgs[c]);
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             // lane chunks of consecutive starts
             const int64_t C = (L + kWave - 1) / kWave;
             const int64_t a0 = min(L, (int64_t)lane * C), a1 = min(L, a0 + C);
@@ -223,9 +234,9 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
                 pick = __shfl(found, who);
             }
             if (lane == 0) cs[i] = (int32_t)pick;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             if (lane < l) atomicAdd(&n[(int)prot_sym(W, s0 + pick + lane) * l + lane], 1);
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         }
         const double Fr = alignment_F(n, bgs, A, l, t, beta);
         if (g.F && lane == 0) g.F[b * it1 + r + 1] = Fr;
@@ -233,14 +244,14 @@ __global__ void __launch_bounds__(kGibbsThreads) k_gibbs(const GibbsArgs g)
             Fb = Fr;
             for (int i = lane; i < t; i += kWave) bs[i] = cs[i];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     // the best alignment's model and sites
     for (int e = lane; e < AL; e += kWave) n[e] = 0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int i = 0; i < t; ++i)
         if (lane < l) atomicAdd(&n[(int)prot_sym(W, O[i] + bs[i] + lane) * l + lane], 1);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int e = lane; e < AL; e += kWave)
         g.theta_out[b * AL + e] = ((double)n[e] + beta * bgs[e / l]) / ((double)t + beta);
     if (g.sites)
@@ -420,9 +431,9 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
     // Starts whose three-letter sum is within rounding of the largest are
     // decided by their sum over the positions in order.
     for (int e = lane; e < AL; e += kWave) Tw[e] = log(g.theta0[b * AL + e]) - log(bgs[e / l]);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     tables3<NG, false>(Tw, l, T3);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     double tol = 0;
     if (lane < l)
         for (int c = 0; c < 4; ++c) tol = fmax(tol, fabs(Tw[c * l + lane]));
@@ -450,10 +461,10 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
         if (lane == 0) cs[i] = (int32_t)ba;
     }
     for (int e = lane; e < AL; e += kWave) n[e] = 0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int i = 0; i < t; ++i)
         if (lane < l) atomicAdd(&n[dna_sym(W, O[i] + cs[i] + lane) * l + lane], 1);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int e = lane; e < AL; e += kWave) Tw[e] = R[e / l * (t + 1) + n[e]];
     double Fb = alignment_F(n, bgs, 4, l, t, beta);
     const int it1 = g.sweeps + 1;
@@ -463,13 +474,13 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
     // one site's letters taken out of (d = -1) or put into (d = 1) the counts,
     // with their ratios
     auto site = [&](int64_t P, int d) {
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         if (lane < l) {
             const int c = (int)dna_sym(W, P + lane), e = c * l + lane, k = n[e] + d;
             n[e] = k;
             Tw[e] = R[c * (t + 1) + k];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     };
     for (int r = 0; r < g.sweeps; ++r) {
         double us = 0;
@@ -482,11 +493,11 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
             int64_t pick;
             if (prod) {
                 tables3<NG, true>(Tw, l, T3);
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 pick = draw_start<NG, true>(W, s0, L, T3, u);
             } else {
                 tables3<NG, false>(Tw, l, T3);
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 pick = draw_start<NG, false>(W, s0, L, T3, u);
             }
             if (lane == 0) cs[i] = (int32_t)pick;
@@ -498,14 +509,14 @@ __global__ void __launch_bounds__(kGibbsThreads, 4) k_gibbs_dna(const GibbsArgs 
             Fb = Fr;
             for (int i = lane; i < t; i += kWave) bs[i] = cs[i];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     // the best alignment's model and sites
     for (int e = lane; e < AL; e += kWave) n[e] = 0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int i = 0; i < t; ++i)
         if (lane < l) atomicAdd(&n[dna_sym(W, O[i] + bs[i] + lane) * l + lane], 1);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     for (int e = lane; e < AL; e += kWave)
         g.theta_out[b * AL + e] = ((double)n[e] + beta * bgs[e / l]) / ((double)t + beta);
     if (g.sites)
