@@ -86,6 +86,9 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+// counts that wait in theta_out's entries
+typedef float float_in __attribute__((may_alias));
+typedef float float2_in __attribute__((ext_vector_type(2), aligned(8), may_alias));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte table quad
 
 struct EmMfmaArgs {
@@ -145,8 +148,8 @@ constexpr int kWaves = 4;  // waves (groups of 16 models) per part of a workgrou
 // models alone would leave SIMDs idle (em_parts) takes the slots side by side,
 // as parts of a workgroup of kWaves waves each with their own tables and
 // counts (and one group of models per wave); else they follow each other, the
-// sum of their counts waiting in theta_out, which the iteration has read and not
-// yet written.
+// counts of all but the last waiting in theta_out, which the iteration has read
+// and not yet written.
 constexpr int kPartThreads = 64 * kWaves;
 __device__ __forceinline__ int part_thread() { return (int)(threadIdx.x % kPartThreads); }
 // tile shape 10 G + PPB: G groups of 16 models per wave, PPB window pairs
@@ -892,9 +895,9 @@ k_em_mfma(const EmMfmaArgs a0)
                 i = next;
                 if (!end) continue;
                 if (PARTS || k + 1 >= used) break;
-                // ---- this slot's counts (own entries), added to the earlier ones',
-                // wait where their column of theta will be; the next slot's start
-                // from zero
+                // ---- this slot's counts (own entries) wait where their column of
+                // theta will be, slot k in half k of the entry; the next slot's
+                // start from zero
 #pragma unroll
                 for (int q = 0; q < G; ++q) {
                     const double em = ls[q].m;
@@ -914,10 +917,9 @@ k_em_mfma(const EmMfmaArgs a0)
                         const int64_t b = b0 + u / 64 * (16 * G) + 16 * q + u % 16;
                         float4v *own = reinterpret_cast<float4v *>(&accs[u / 64][q][u % 16][p][0]);
                         if (p < l && b < nvalid) {
-                            double *wait = a.theta_out + b * AL + p;
+                            float_in *wait = reinterpret_cast<float_in *>(a.theta_out + b * AL + p) + k;
 #pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                wait[c * l] = (double)(k > 0 ? (float)wait[c * l] + (*own)[c] : (*own)[c]);
+                            for (int c = 0; c < 4; ++c) wait[2 * c * l] = (*own)[c];
                         }
                         *own = float4v{0.f, 0.f, 0.f, 0.f};
                     }
@@ -979,7 +981,10 @@ k_em_mfma(const EmMfmaArgs a0)
                             cn += *reinterpret_cast<const float4v *>(&acc_of(k)[wv][q][r][p][0]);
                         if (!PARTS && used > 1)
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) cn[c] = (float)a.theta_out[b * AL + c * l + p] + cn[c];
+                            for (int c = 0; c < 4; ++c) {
+                                const float2_in w = *reinterpret_cast<float2_in *>(a.theta_out + b * AL + c * l + p);
+                                cn[c] = (used > 2 ? w[0] + w[1] : w[0]) + cn[c];
+                            }
                         // every column's counts sum to t: normalising by the column's
                         // own total is the same update and stays on the simplex
                         const double tot = (double)cn[0] + (double)cn[1] + (double)cn[2] + (double)cn[3] + beta;
@@ -1102,11 +1107,15 @@ constexpr int kCUs = 256;
 // workgroup of 64 models at most, else one.  16 384 models of the (21,7)
 // workload in single FP16, one workgroup per CU: 6.3 ms in one part, 3.8 in
 // three; just above (16 500 to 24 500 models, 3 iterations) 5.7 ms in one part
-// against 6.1 in two, and on (18,6) in split FP16 1.55 against 1.65.
+// against 6.1 in two, and on (18,6) in split FP16 1.55 against 1.65.  Where the
+// number of models is on the device, or an instance's last workgroup may be
+// partly filled, the capacity may be more than there is: up to twice as much
+// still goes in parts, which cost 0 to 6% if it is full ((18,6): two rounds of
+// 0.81 ms against 1.52 to 1.64 in one part) and take half the time if it is not.
 static int em_parts(const EmMfmaArgs &a)
 {
     const int slots = em_slots((a.l + 3) / 4, a.split != 0);
-    if (em_groups(a, 16 * kWaves) > kCUs) return 1;
+    if (em_groups(a, 16 * kWaves) > (a.inst || a.n_dev ? 2 * kCUs : kCUs)) return 1;
     return a.site_stride < slots ? a.site_stride : slots;
 }
 
