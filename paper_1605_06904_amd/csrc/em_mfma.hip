@@ -643,6 +643,7 @@ __device__ __forceinline__ void sweep(const EmMfmaArgs &a, const uint32_t *W, co
         if (!LAST) {
             double x = __builtin_amdgcn_rcp(sr);
             x = fma(fma(-sr, x, 1.0), x, x);
+            x = fma(fma(-sr, x, 1.0), x, x);
             const float inv = (float)x;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
