@@ -151,9 +151,10 @@ __global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_e
                     for (int x = lane; x < L; x += 64) {
                         const Win w = load_win(W, s0 + x);
                         const T s = score3<T, NG>(w, W3);
-                        // the larger component, and what the other is of it
+                        // the larger component, and what the other is of it (a NaN
+                        // score, or an infinite one, makes its posterior NaN)
                         const T v = lm + s;
-                        const bool site = v > ln0;
+                        const bool site = !(v <= ln0);
                         const T e = v == ninf<T>() ? (T)0 : ln0 == ninf<T>() ? (T)0 : ex(site ? ln0 - v : v - ln0);
                         lsum += (double)((site ? v : ln0) + lg1p(e));
                         if (last) {
@@ -164,7 +165,7 @@ __global__ void __launch_bounds__(64 * WAVES, NG == 8 && WAVES == 4 ? 2 : 4) k_e
                             }
                             continue;
                         }
-                        const T z = (site ? (T)1 : e) / ((T)1 + e);
+                        const T z = (site ? (T)1 + (v - v) : e) / ((T)1 + e);
                         scatter3<NG>(w, z, ac);
                     }
                     llr_w += wave_sum(lsum);

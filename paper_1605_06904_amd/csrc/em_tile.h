@@ -280,7 +280,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) k_em_tile(const EmArgs a)
                 int terms = 0;
                 auto posterior = [&](int w0) {
                     const double v = lmix + tile_score<NG>(at + w0, W3m);
-                    const bool site = v > lnone;
+                    const bool site = !(v <= lnone);  // (a NaN or infinite score: a NaN posterior)
                     const double e = v == ninf<double>() || lnone == ninf<double>()
                                          ? 0.0
                                          : exp_le0(site ? lnone - v : v - lnone, exps);
@@ -291,7 +291,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) k_em_tile(const EmArgs a)
                     const bool in = w0 + g < hi;
                     llr += in ? site ? v : lnone : 0.0;
                     prod *= in ? d : 1.0;
-                    return in ? site ? y : e * y : 0.0;
+                    return in ? site ? y + (v - v) : e * y : 0.0;
                 };
                 for (int w0 = lo; w0 < hi; w0 += 8) {
                     const double P0 = posterior(w0), P1 = posterior(w0 + 4);
