@@ -467,7 +467,9 @@ __device__ __forceinline__ void prot_wave(const EmProtArgs &a, uint8_t *dyn, Pro
                 tot += p > 0 ? ldexp(p, (int)(sh.pref[w][lane] - M)) : p;
             }
             const double lz = (double)M + log2(tot);  // log2 of the sum of 2^S
-            llr += lz * 0.6931471805599453 - log((double)L);
+            // a sum that is not a number (a zero in theta, whose log-odds the one-hot
+            // multiplies by 0): log-likelihood -inf
+            llr += (lz == lz ? lz : -INFINITY) * 0.6931471805599453 - log((double)L);
             if (last) {
                 if (a.sites && wv == 0 && b0 + lane < nvalid) {
                     float bv = sh.pbest[0][lane];

@@ -92,3 +92,23 @@ def test_two_iterations_at_block_edges(l, windows, B):
         win = np.lib.stride_tricks.sliding_window_view(c, l)
         s = lo[:, win, np.arange(l)].sum(axis=2)
         assert (s[np.arange(B), sites[:, i]] >= s.max(axis=1) - 2 * delta).all()
+
+
+def test_zero_in_theta0():
+    """Its log-odds is -inf, which the one-hot multiplies by 0: the sequence's
+    log-likelihood is -inf, and other models' are not touched."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] protein f16, a zero in theta0", flush=True)
+    rng = np.random.default_rng(8)
+    l, B = 6, 3
+    seqs = random_sequences(rng, 3, [80, 200, 41], "protein")
+    th0 = rng.dirichlet(np.full(20, 2.0), size=(B, l)).transpose(0, 2, 1).copy()
+    th0[1, :, 2] = 0.0
+    d = lambda x: torch.as_tensor(np.ascontiguousarray(x), device="cuda")
+    th = torch.zeros((B, 20, l), dtype=torch.float64, device="cuda")
+    J = torch.zeros((B, 1), dtype=torch.float64, device="cuda")
+    LL = torch.zeros_like(J)
+    pm.em_refine(pm.Seqs(20, seqs), l, d(th0), d(np.full(20, 0.05)), B, None, 0, 1.0, pm.PM_F16, th, J, LL)
+    LL = LL.cpu().numpy()[:, 0]
+    assert LL[1] == -np.inf and np.isfinite(LL[[0, 2]]).all()
