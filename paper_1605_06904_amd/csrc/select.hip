@@ -856,7 +856,8 @@ __device__ __forceinline__ void emit_heavy(const SelArgs &a, int j, int64_t ne, 
             for (uint32_t p = tid; p < nm; p += kHeavyThreads) {
                 const uint32_t i = lb[p];
                 if (i == kNoBucket) continue;
-                const uint32_t f = first[i], w = lw[p], q0 = f - f0, q1 = min(first[i + 1] - f0, lcap);
+                // (to the last place taken: the caller's counts may exceed the keys')
+                const uint32_t f = first[i], w = lw[p], q0 = f - f0, q1 = min(cur[i], lcap);
                 uint32_t rank = 0;
                 for (uint32_t q = q0; q < q1; q += 4) {
                     uint32_t v[4];
