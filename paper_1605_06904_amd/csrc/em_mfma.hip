@@ -87,8 +87,7 @@ typedef _Float16 half16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 // counts that wait in theta_out's entries
-typedef float float_in __attribute__((may_alias));
-typedef float float2_in __attribute__((ext_vector_type(2), aligned(8), may_alias));
+typedef float float4_in __attribute__((ext_vector_type(4), aligned(8), may_alias));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte table quad
 
 struct EmMfmaArgs {
@@ -896,9 +895,8 @@ k_em_mfma(const EmMfmaArgs a0)
                 i = next;
                 if (!end) continue;
                 if (PARTS || k + 1 >= used) break;
-                // ---- this slot's counts (own entries) wait where their column of
-                // theta will be, slot k in half k of the entry; the next slot's
-                // start from zero
+                // ---- this slot's counts (own entries) wait in the model's rows of
+                // theta_out, four letters together; the next slot's start from zero
 #pragma unroll
                 for (int q = 0; q < G; ++q) {
                     const double em = ls[q].m;
@@ -917,11 +915,8 @@ k_em_mfma(const EmMfmaArgs a0)
                         const int q = j / MT, p = 4 * (j % MT) + u % 64 / 16;
                         const int64_t b = b0 + u / 64 * (16 * G) + 16 * q + u % 16;
                         float4v *own = reinterpret_cast<float4v *>(&accs[u / 64][q][u % 16][p][0]);
-                        if (p < l && b < nvalid) {
-                            float_in *wait = reinterpret_cast<float_in *>(a.theta_out + b * AL + p) + k;
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) wait[2 * c * l] = (*own)[c];
-                        }
+                        if (p < l && b < nvalid)
+                            reinterpret_cast<float4_in *>(a.theta_out + b * AL)[k * l + p] = *own;
                         *own = float4v{0.f, 0.f, 0.f, 0.f};
                     }
                 }
@@ -972,6 +967,24 @@ k_em_mfma(const EmMfmaArgs a0)
                 a.J[b * (a.iters + 1) + it] = llr[q] + beta * prior[q];
                 if (a.llr) a.llr[b * (a.iters + 1) + it] = llr[q];
             }
+            if (!PARTS && !last && used > 1) {
+                // the slots' counts in order; every lane of the wave has read what
+                // waits in its models' rows before any writes them
+                const float4_in *wait = reinterpret_cast<const float4_in *>(a.theta_out + b * AL);
+                #pragma unroll 1
+                for (int mt = 0; mt < MT; ++mt) {
+                    const int p = 4 * mt + g;
+                    if (p < l && vb) {
+                        float4v cn = wait[p];
+                        if (used > 2) cn += wait[l + p];
+                        float4v *own = reinterpret_cast<float4v *>(&acc[q][r][p][0]);
+                        *own = cn + *own;
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
             if (!last && vb) {
                 #pragma unroll 1
                 for (int mt = part; mt < MT; mt += parts) {
@@ -980,12 +993,6 @@ k_em_mfma(const EmMfmaArgs a0)
                         float4v cn = *reinterpret_cast<const float4v *>(&acc_of(0)[wv][q][r][p][0]);
                         for (int k = 1; k < parts; ++k)
                             cn += *reinterpret_cast<const float4v *>(&acc_of(k)[wv][q][r][p][0]);
-                        if (!PARTS && used > 1)
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) {
-                                const float2_in w = *reinterpret_cast<float2_in *>(a.theta_out + b * AL + c * l + p);
-                                cn[c] = (used > 2 ? w[0] + w[1] : w[0]) + cn[c];
-                            }
                         // every column's counts sum to t: normalising by the column's
                         // own total is the same update and stays on the simplex
                         const double tot = (double)cn[0] + (double)cn[1] + (double)cn[2] + (double)cn[3] + beta;
