@@ -265,6 +265,12 @@ int theta_init(int32_t alphabet, int32_t l, const uint32_t *profile, int64_t B,
  *   sites_out  device [B][t] int32 or NULL: argmax_a s_ia under theta^iters,
  *              first on ties
  *   precision  PM_FP64, PM_FP32, PM_F16X2 or PM_F16
+ * A model's results do not depend on the other models of a call, with one
+ * exception in the last bits: PM_FP64 and PM_FP32 calls on DNA models of one
+ * instance (l <= 24) with enough of them (from about 2250 on, counted on the
+ * device where n_dev is given) run sixteen models at a time in another order
+ * of sums.  em_refine_batch and projection_run never do, and PM_F16X2 and
+ * PM_F16 results are the same bit for bit in every call.
  *   ws, ws_bytes  device workspace of at least pm_em_workspace(S, l, precision)
  *              bytes, 16-byte aligned, or NULL.  The DNA matrix-core forms keep
  *              the one-hot tables of every 32-window pair there (built once per

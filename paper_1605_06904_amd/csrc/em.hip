@@ -492,7 +492,8 @@ extern "C" int em_refine(const pm_seqs *S, int32_t l, const double *theta0, cons
 }
 
 // em_refine in the batch's form, whatever the number of models: a problem
-// gives the same answer alone, in a batch and in ranges of its trials
+// gives the same answer alone, in a batch and in ranges of its trials (the
+// matrix-core forms give it in any call)
 int pm::em_refine_as_batch(const pm_seqs *S, int32_t l, const double *theta0, const double *bg, int64_t B,
                            const int64_t *n_dev, int32_t iters, double beta, int32_t precision, double *theta_out,
                            double *J_out, double *llr_out, int32_t *sites_out, void *ws, size_t ws_bytes, void *stream)

@@ -62,17 +62,20 @@
 // shape: em_autotune times the variants on the caller's models and records
 // the fastest per (ceil(l/4), precision) class.
 //
-// What bounds it: vector issue.  An MFMA takes two of the vector unit's issue
-// slots (8 cycles) and overlaps the rest of its 16, so a pair of 16 MFMAs and
-// 44 vector instructions, 8 of them exponentials, takes about 350 cycles of a
-// SIMD; 600 are measured at three waves per SIMD ((18,6), 89 000 models, 10
-// iterations: 10.4 ms).  Measured on that workload: 12.0 ms with the dense
+// What bounds it: no pipe alone.  Counters of (18,6), 89 000 models, 10
+// iterations, default shape: the matrix pipe is busy 37% of the time and the
+// vector unit 56%; a wave issues in 36% of its cycles, waits for an issue slot
+// (with two others on its SIMD) in 37%, and for data or a barrier in 27%.  An
+// MFMA takes two of the vector unit's issue slots (8 cycles) and overlaps the
+// rest of its 16, so a pair of 16 MFMAs and 44 vector instructions, 8 of them
+// exponentials, would take about 350 cycles of a SIMD; 600 are measured at
+// three waves per SIMD.  Measured on that workload: 12.0 ms with the dense
 // E-step, references started from the lowest score and two FP64 logarithms
 // per sequence; 11.8 with the sparse E-step (16 instead of 20 MFMAs a pair),
 // 10.3 in a timing copy whose references never move.  (15,4) batch of 24
 // instances: 18.1 -> 15.4 ms; single FP16, (21,7), 16 384 models, 5 iterations:
 // 6.8 -> 6.3 ms, 3.8 ms in three parts.  The slots one after the other cost
-// 2 to 3% (10.4 -> 10.8 ms, 15.6 -> 15.9 ms) against one sum over all
+// 1 to 3% (10.48 -> 10.58 ms, 15.2 -> 15.6 ms) against one sum over all
 // sequences.
 #include <math.h>
 #include <stddef.h>
