@@ -29,6 +29,7 @@ FP16_MFMA_PEAK = 2500.0      # TFLOP/s, MI355X dense FP16 matrix cores
 # the kernel source is the one they were taken on (sha256 prefix).
 MEASURED_TRAFFIC = {
     "hash.hip": ("8544af7b0b679691", {"k_hash<4,8>": 1.705e9, "k_hash<4,9>": 14.492e9, "k_hash<20,4>": 1.517e9}),
+    "em_mfma.hip": ("71907530fca8855e", {"k_em_mfma<5,2,true,1,1,false>": 2.163e9, "k_em_mfma<5,2,true,2,1,false>": 2.474e9, "k_em_mfma<5,2,true,4,1,false>": 2.728e9, "k_em_mfma<5,2,true,1,2,false>": 2.086e9, "k_em_mfma<5,2,true,2,2,false>": 2.193e9, "k_em_mfma<5,2,true,4,2,false>": 2.319e9}),
 }
 
 

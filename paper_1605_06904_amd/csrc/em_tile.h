@@ -32,7 +32,7 @@
 // sequences of 1000, 10 iterations: FP64 OOPS of l = 14, 18, 22: 6.9, 7.6, 8.9
 // -> 3.2, 3.7, 4.5 ms; ZOOPS in FP32, l = 18: 7.5 -> 3.8 ms; TCM in FP64: 6.2,
 // 6.8, 8.0 -> 3.7, 4.1, 4.7 ms; a (15,4) pass of 20 600 models, 5 iterations
-// (six rounds of which the last is nearly empty): 11.4 -> 7.8 ms.  FP32 calls
+// (six rounds of which the last is nearly empty): 11.4 -> 7.3 ms.  FP32 calls
 // take this form too: all arithmetic in FP64, sites by FP32 scores.
 //
 // It needs sixteen models per CU to fill the chip (tile_takes).
